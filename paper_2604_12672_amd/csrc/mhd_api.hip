@@ -164,6 +164,59 @@ int latched(mhd_ctx *h) {
   return MHD_OK;
 }
 
+// The stage kernel's work over its resident blocks (CUs x blocks per CU).  A
+// segment of n planes costs n + STAGE_STEPS steps of the march (filling and
+// draining its pipeline), and the blocks work in rounds of one segment each.
+// Every block first takes `full` whole columns; the columns of the tiles
+// that are left are cut in equal segments.  The pair that costs the fewest
+// steps is taken.  MHD_ZSEG (planes per segment, no whole columns) overrides
+// the choice for tuning and tests.
+constexpr long long STAGE_STEPS = 5;
+void split_stage_work(mhd::Ctx &c, int dev) {
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1)
+    cus = 256;
+  const long long slots = (long long)cus * mhd::stage_blocks_per_cu(c), nz = c.ph.nz;
+  const long long tiles = (long long)((c.ph.nx + mhd::TB - 1) / mhd::TB) *
+                          ((c.ph.ny + mhd::TB - 1) / mhd::TB);
+  long long best = -1, items = 1;
+  for (long long full = 0; full <= (c.d.precision == MHD_PREC_SPLIT ? 0 : tiles / slots); ++full) {
+    const long long rest = tiles - full * slots;
+    for (long long segs = 1; segs <= (nz < 64 ? nz : 64); ++segs) {
+      const long long len = (nz + segs - 1) / segs, n = rest * ((nz + len - 1) / len);
+      const long long cost = full * (nz + STAGE_STEPS) +
+                             (n + slots - 1) / slots * (len + STAGE_STEPS);
+      if (best < 0 || cost < best) {
+        best = cost;
+        c.stage_full = (int)full;
+        c.stage_share = (int)len;
+        items = n;
+      }
+    }
+  }
+  if (const char *zs = std::getenv("MHD_ZSEG")) {
+    const int v = std::atoi(zs);
+    if (v >= 1 && v <= mhd::ZSEG_MAX) {
+      c.stage_full = 0;
+      c.stage_share = v < nz ? v : (int)nz;
+      items = tiles * ((nz + c.stage_share - 1) / c.stage_share);
+    }
+  }
+  c.stage_tiles = (int)tiles;
+  c.stage_blocks = (int)(c.stage_full > 0 || (items > slots && c.d.precision != MHD_PREC_SPLIT) ? slots : items);
+  c.zseg = c.stage_full > 0 ? (int)nz : c.stage_share;
+}
+
+// the stage kernel's table to the device (synchronises)
+int upload_table(mhd_ctx *h) {
+  mhd::Ctx &c = h->c;
+  HIPCHK(h, hipMemcpyAsync(c.table, c.table_host.data(), sizeof(double) * c.table_host.size(),
+                           hipMemcpyHostToDevice, c.stream));
+  HIPCHK(h, hipStreamSynchronize(c.stream));
+  return MHD_OK;
+}
+
 }  // namespace
 
 namespace mhd {
@@ -247,38 +300,7 @@ int mhd_init_grid(const mhd_grid_desc *desc, void *hip_stream, mhd_ctx **out) {
   mhd::fill_phys(desc, ph);
   c.ncell = (size_t)desc->nx * desc->ny * desc->nz;
   c.nfz = (size_t)desc->nx * desc->ny * ph.nzf;
-  // z planes per stage block: a longer segment re-reads fewer halo planes
-  // (4 extra per segment), a shorter one gives more blocks.  The blocks run
-  // in rounds of (CUs x resident blocks per CU); pick the segment that
-  // minimises rounds x (planes + 4) over 16..48 planes.  MHD_ZSEG
-  // overrides the choice for tuning.
-  {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-      cus = 256;
-    const long long slots = (long long)cus * mhd::stage_blocks_per_cu(c);
-    const long long tiles = (long long)((desc->nx + mhd::TB - 1) / mhd::TB) *
-                            ((desc->ny + mhd::TB - 1) / mhd::TB);
-    const int nz = desc->nz;
-    c.zseg = nz < 16 ? nz : 16;
-    long long best = -1;
-    for (int zs = 16; zs <= 48 && zs <= nz; ++zs) {
-      const int segs = (nz + zs - 1) / zs;
-      const int len = (nz + segs - 1) / segs;  // balanced segments
-      const long long rounds = (tiles * segs + slots - 1) / slots;
-      const long long cost = rounds * (len + 4);
-      if (best < 0 || cost < best) {
-        best = cost;
-        c.zseg = len;
-      }
-    }
-  }
-  if (const char *zs = std::getenv("MHD_ZSEG")) {
-    const int v = std::atoi(zs);
-    if (v >= 1 && v <= mhd::ZSEG_MAX) c.zseg = v;
-  }
-  if (c.zseg > desc->nz) c.zseg = desc->nz;
+  split_stage_work(c, dev);
 
   auto cleanup = [&](hipError_t e, const char *what) {
     g_init_err = std::string(what) + ": " + hipGetErrorString(e);
@@ -309,14 +331,12 @@ int mhd_init_grid(const mhd_grid_desc *desc, void *hip_stream, mhd_ctx **out) {
     for (int s = 0; s < 2; ++s)
       if ((e = hipMalloc(&c.T[s], sizeof(double) * c.ncell)) != hipSuccess)
         return cleanup(e, "hipMalloc T");
-  if ((e = hipMalloc(&c.bg_cc, sizeof(double) * 4 * ph.nz)) != hipSuccess)
-    return cleanup(e, "hipMalloc bg");
-  if ((e = hipMalloc(&c.bg_fz, sizeof(double) * 4 * ph.nzf)) != hipSuccess)
-    return cleanup(e, "hipMalloc bg");
-  if ((e = hipMemsetAsync(c.bg_cc, 0, sizeof(double) * 4 * ph.nz, c.stream)) != hipSuccess)
-    return cleanup(e, "hipMemset bg");
-  if ((e = hipMemsetAsync(c.bg_fz, 0, sizeof(double) * 4 * ph.nzf, c.stream)) != hipSuccess)
-    return cleanup(e, "hipMemset bg");
+  c.table_host.assign((size_t)mhd::TAB_N * ph.nzf, 0.0);
+  if ((e = hipMalloc(&c.table, sizeof(double) * c.table_host.size())) != hipSuccess)
+    return cleanup(e, "hipMalloc table");
+  if ((e = hipMemsetAsync(c.table, 0, sizeof(double) * c.table_host.size(), c.stream)) !=
+      hipSuccess)
+    return cleanup(e, "hipMemset table");
   c.red_len = 16384;
   if ((e = hipMalloc(&c.red, sizeof(double) * c.red_len)) != hipSuccess)
     return cleanup(e, "hipMalloc red");
@@ -360,11 +380,8 @@ int mhd_destroy(mhd_ctx *h) {
   }
   (void)hipFree(c.T[0]);
   (void)hipFree(c.T[1]);
-  (void)hipFree(c.bg_cc);
-  (void)hipFree(c.bg_fz);
-  (void)hipFree(c.heat);
+  (void)hipFree(c.table);
   (void)hipFree(c.fcoef);
-  (void)hipFree(c.fzb);
   (void)hipFree(c.red);
   (void)hipFree(c.dt_dev);
   (void)hipFree(c.flags);
@@ -405,10 +422,12 @@ int mhd_set_background(mhd_ctx *h, const double *w_cc, const double *w_fz) {
     for (int k = 0; k < nzf; ++k)
       if (!std::isfinite(w_fz[f * nzf + k])) return fail(h, MHD_ERR_ARG, "background not finite");
   }
-  HIPCHK(h, hipMemcpyAsync(c.bg_cc, w_cc, sizeof(double) * 4 * nz, hipMemcpyHostToDevice, c.stream));
-  HIPCHK(h, hipMemcpyAsync(c.bg_fz, w_fz, sizeof(double) * 4 * nzf, hipMemcpyHostToDevice, c.stream));
-  HIPCHK(h, hipStreamSynchronize(c.stream));
-  return MHD_OK;
+  for (int f = 0; f < 4; ++f) {
+    for (int k = 0; k < nz; ++k) c.table_host[(size_t)k * mhd::TAB_N + f] = w_cc[f * nz + k];
+    for (int k = 0; k < nzf; ++k)
+      c.table_host[(size_t)k * mhd::TAB_N + mhd::TAB_FACE + f] = w_fz[f * nzf + k];
+  }
+  return upload_table(h);
 }
 
 int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_t nmodes) {
@@ -428,13 +447,9 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
   if (heat) {
     for (int k = 0; k < c.ph.nz; ++k)
       if (!std::isfinite(heat[k])) return fail(h, MHD_ERR_ARG, "heating must be finite");
-    if (!c.heat) HIPCHK(h, hipMalloc(&c.heat, sizeof(double) * c.ph.nz));
-    HIPCHK(h, hipMemcpyAsync(c.heat, heat, sizeof(double) * c.ph.nz, hipMemcpyHostToDevice, c.stream));
-  } else if (c.heat) {
-    HIPCHK(h, hipStreamSynchronize(c.stream));
-    (void)hipFree(c.heat);
-    c.heat = nullptr;
   }
+  for (int k = 0; k < c.ph.nz; ++k)
+    c.table_host[(size_t)k * mhd::TAB_N + 4] = heat ? heat[k] : 0.0;
   if (nmodes > 0) {
     // f(x) = sum_m a_m cos(alpha_m(x, y) + 2 pi k_z,m Z), alpha_m = 2 pi
     // (k_x X + k_y Y) + phi_m, X = (x - lo)/L at cell centres.  With
@@ -445,7 +460,7 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
     const int nx = c.ph.nx, ny = c.ph.ny, nz = c.ph.nz;
     const double pi2 = 6.283185307179586476925286766559;
     const size_t nxy = (size_t)nx * ny;
-    std::vector<double> coef((size_t)3 * mhd::FZB * nxy, 0.0), zb((size_t)mhd::FZB * nz);
+    std::vector<double> coef((size_t)3 * mhd::FZB * nxy, 0.0);
     // cos and sin of alpha = a_x + a_y with a_x = 2 pi k_x X + phi and
     // a_y = 2 pi k_y Y from per-axis tables (angle addition), so a mode
     // costs nx + ny sine/cosine pairs instead of nx ny
@@ -480,27 +495,28 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
     }
     for (int k = 0; k < nz; ++k) {
       const double Z = (k + 0.5) / nz;
-      zb[k] = 1.0;
-      zb[(size_t)nz + k] = std::cos(pi2 * Z);
-      zb[(size_t)2 * nz + k] = std::sin(pi2 * Z);
-      zb[(size_t)3 * nz + k] = std::cos(2.0 * pi2 * Z);
-      zb[(size_t)4 * nz + k] = std::sin(2.0 * pi2 * Z);
+      double *zb = c.table_host.data() + (size_t)k * mhd::TAB_N + 5;
+      zb[0] = 1.0;
+      zb[1] = std::cos(pi2 * Z);
+      zb[2] = std::sin(pi2 * Z);
+      zb[3] = std::cos(2.0 * pi2 * Z);
+      zb[4] = std::sin(2.0 * pi2 * Z);
     }
-    if (!c.fcoef) HIPCHK(h, hipMalloc(&c.fcoef, sizeof(double) * coef.size()));
-    if (!c.fzb) HIPCHK(h, hipMalloc(&c.fzb, sizeof(double) * zb.size()));
-    HIPCHK(h, hipMemcpyAsync(c.fcoef, coef.data(), sizeof(double) * coef.size(),
-                             hipMemcpyHostToDevice, c.stream));
-    HIPCHK(h, hipMemcpyAsync(c.fzb, zb.data(), sizeof(double) * zb.size(), hipMemcpyHostToDevice,
-                             c.stream));
+    // the split path keeps the coefficients in FP32 (6e-8 of the forcing)
+    const bool split = c.d.precision == MHD_PREC_SPLIT;
+    std::vector<float> coef32;
+    if (split) coef32.assign(coef.begin(), coef.end());
+    const void *src = split ? (const void *)coef32.data() : (const void *)coef.data();
+    const size_t bytes = coef.size() * (split ? sizeof(float) : sizeof(double));
+    if (!c.fcoef) HIPCHK(h, hipMalloc(&c.fcoef, bytes));
+    HIPCHK(h, hipMemcpyAsync(c.fcoef, src, bytes, hipMemcpyHostToDevice, c.stream));
     HIPCHK(h, hipStreamSynchronize(c.stream));  // the host tables go out of scope
   } else if (c.fcoef) {
     HIPCHK(h, hipStreamSynchronize(c.stream));
     (void)hipFree(c.fcoef);
-    (void)hipFree(c.fzb);
-    c.fcoef = c.fzb = nullptr;
+    c.fcoef = nullptr;
   }
-  HIPCHK(h, hipStreamSynchronize(c.stream));
-  return MHD_OK;
+  return upload_table(h);
 }
 
 int mhd_set_state(mhd_ctx *h, const double *U, const double *Bx, const double *By,
@@ -624,11 +640,8 @@ static int run_step(mhd_ctx *h, double dt_host, const double *dt_dev) {
       HIPCHK(h, mhd::launch_shock_flags(c));
       p.flat = c.shock_f;
     }
-    p.bg_cc = c.bg_cc;
-    p.bg_fz = c.bg_fz;
-    p.heat = c.heat;
+    p.table = c.table;
     p.fcoef = c.fcoef;
-    p.fzb = c.fzb;
     p.dt_dev = dt_dev;
     p.flags = c.flags;
     p.newton_stats = c.nstats;
@@ -984,8 +997,7 @@ int mhd_launch_info(const mhd_ctx *h, int32_t *tile, int32_t *zseg, int32_t *blo
   if (tile) *tile = mhd::TB;
   if (zseg) *zseg = c.zseg;
   if (blocks)
-    *blocks = ((c.ph.nx + mhd::TB - 1) / mhd::TB) * ((c.ph.ny + mhd::TB - 1) / mhd::TB) *
-              ((c.ph.nz + c.zseg - 1) / c.zseg);
+    *blocks = c.stage_blocks;
   return MHD_OK;
 }
 

@@ -310,20 +310,35 @@ __device__ __forceinline__ v4s pack_bf16(float a, float b, float c, float d) {
   return __builtin_bit_cast(v4s, w);
 }
 
-// ReLU of two FP32 values into one register of packed BF16: the pair is
-// converted in one instruction, then a negative BF16 (a negative 16-bit
-// integer, -0 included) is cleared by an integer max with 0 on both halves
-// (v_pk_max_i16).  The empty asm statement (no instruction) hides the
-// packed register from the instruction combiner, which would otherwise
-// split the pair into two single conversions and a permute.
-__device__ __forceinline__ unsigned pack2_relu(float a, float b) {
-  unsigned u = pack2_bf16(a, b);
-  asm("" : "+v"(u));
-  return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(v2s, u), (v2s)0));
-}
-__device__ __forceinline__ v4s pack_relu(const v16f &d, int j) {
-  const v2u w = {pack2_relu(d[4 * j], d[4 * j + 1]), pack2_relu(d[4 * j + 2], d[4 * j + 3])};
-  return __builtin_bit_cast(v4s, w);
+// ReLU of the 32 values of a layer's two products into packed BF16 (h[j]:
+// values 4j .. 4j+3, the second product's from h[4]): the pairs are converted
+// in one instruction each, then a negative BF16 (a negative 16-bit integer,
+// -0 included) is cleared by an integer max with 0 on both halves
+// (v_pk_max_i16).  The empty asm statement (no instruction) hides the packed
+// registers from the instruction combiner, which would otherwise split each
+// pair into two single conversions and a permute; there is one for the whole
+// layer, behind the first use of both products, so that it does not stand in
+// the wait for either.
+__device__ __forceinline__ void pack2_relu(const v16f &d0, const v16f &d1, v4s *h) {
+  unsigned u[16];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    u[j] = pack2_bf16(d0[2 * j], d0[2 * j + 1]);
+    u[8 + j] = pack2_bf16(d1[2 * j], d1[2 * j + 1]);
+  }
+  asm(""
+      : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(u[4]), "+v"(u[5]), "+v"(u[6]),
+        "+v"(u[7]), "+v"(u[8]), "+v"(u[9]), "+v"(u[10]), "+v"(u[11]), "+v"(u[12]), "+v"(u[13]),
+        "+v"(u[14]), "+v"(u[15]));
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    v2u w;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      w[k] = __builtin_bit_cast(unsigned, __builtin_elementwise_max(
+                                              __builtin_bit_cast(v2s, u[2 * j + k]), (v2s)0));
+    h[j] = __builtin_bit_cast(v4s, w);
+  }
 }
 
 // One pass over the 32 cells held by lanes 0..31 (lanes l and l+32 carry
@@ -337,11 +352,7 @@ __device__ __forceinline__ float mlp_pass(const MlpLds &S, float x0, float x1, i
   const v16f c0 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(S.a1[0][lane], b, z, 0, 0, 0);
   const v16f c1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(S.a1[1][lane], b, z, 0, 0, 0);
   v4s h[8];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    h[j] = pack_relu(c0, j);
-    h[4 + j] = pack_relu(c1, j);
-  }
+  pack2_relu(c0, c1, h);
   v16f d0, d1;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -362,9 +373,10 @@ __device__ __forceinline__ float mlp_pass(const MlpLds &S, float x0, float x1, i
   // with the matching W3 pairs, then the other half of the wave's rows
   const int kh = 4 * (lane >> 5);
   float y = 0.0f;
+  pack2_relu(d0, d1, h);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const v4s hj = j < 4 ? pack_relu(d0, j) : pack_relu(d1, j - 4);
+    const v4s hj = h[j];
     const int row = (j < 4 ? 8 * j : 32 + 8 * (j - 4)) + kh;
     const v2s wlo = *reinterpret_cast<const v2s *>(&S.w3[row]);
     const v2s whi = *reinterpret_cast<const v2s *>(&S.w3[row + 2]);

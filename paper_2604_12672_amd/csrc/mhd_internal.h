@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <string>
+#include <vector>
 
 #include "../../include/mhd.h"
 
@@ -18,8 +19,9 @@ constexpr int TB = TT - 2;    // output columns per tile edge
 constexpr int NTHREADS = TT * TT;
 // z basis of the forcing modes: wavenumbers |k_z| <= 2
 constexpr int FZB = 5;
-// Longest z segment of a stage block (the block stages the background
-// profile of its segment and halo in LDS).
+// entries of a row of the stage kernel's table, first of the face's
+constexpr int TAB_N = 14, TAB_FACE = 10;
+// Most planes a stage block can be set to by MHD_ZSEG.
 constexpr int ZSEG_MAX = 64;
 
 // Physics and grid constants passed by value to every kernel.
@@ -50,13 +52,15 @@ struct StagePtrs {
   double *Uo, *Bxo, *Byo, *Bzo;        // stage output
   const double *Tin;                   // EOS guess (gas+radiation)
   double *Tout;                        // EOS solution (owned cells)
-  const double *bg_cc, *bg_fz;         // [4][nz], [4][nzf]
-  const double *heat;                  // nullable
+  // per z plane k: TAB_N values [nzf][TAB_N], of the cells 0..3 background
+  // rho, P, gamma_e, gamma_c, 4 heating, 5..9 the z basis {1, cos 2piZ,
+  // sin 2piZ, cos 4piZ, sin 4piZ} of the forcing at the cell centre, and of
+  // the face k (TAB_FACE on) the background at its height
+  const double *table;
   // forcing from Fourier modes (nullable): per column the coefficients of
-  // the z basis {1, cos 2piZ, sin 2piZ, cos 4piZ, sin 4piZ} for each
-  // component, fcoef [3 * FZB][ny][nx], and that basis at the cell
-  // centres, fzb [FZB][nz]
-  const double *fcoef, *fzb;
+  // the z basis for each component, fcoef [3 * FZB][ny][nx] (FP32 in the
+  // split path, else FP64)
+  const void *fcoef;
   const double *dt_dev;                // device dt (nullable: use dt_host)
   int newton_cap;                      // Newton steps before the bracketed solve
   const uint8_t *flat = nullptr;       // shock-flattening flags [n] (nullable)
@@ -97,9 +101,9 @@ struct Ctx {
   int cur = 0;  // index of the current state
   double *T[2] = {nullptr, nullptr};
   int tcur = 0;
-  double *bg_cc = nullptr, *bg_fz = nullptr;
-  double *heat = nullptr;
-  double *fcoef = nullptr, *fzb = nullptr;  // forcing tables (see StagePtrs)
+  std::vector<double> table_host;  // the stage kernel's table (see StagePtrs)
+  double *table = nullptr;
+  void *fcoef = nullptr;          // forcing coefficients (see StagePtrs)
   double *dt_dev = nullptr;       // [1]
   void *mlp = nullptr;            // packed guess network on the device
   bool have_mlp = false;
@@ -126,7 +130,10 @@ struct Ctx {
   // flattening: shock_p holds the pressure of the current state (also left
   // by the CFL kernel), so the first stage needs no pressure pass
   bool p_current = false;
-  int zseg = 32;
+  // work split of the stage kernel: every one of stage_blocks blocks takes
+  // stage_full whole columns of planes, the columns of the remaining tiles
+  // are cut in segments of stage_share planes; zseg is the longest segment
+  int stage_tiles = 1, stage_blocks = 1, stage_full = 0, stage_share = 1, zseg = 1;
   std::string err;
 };
 

@@ -1,29 +1,28 @@
 // mhd_kernels.hip -- gfx950 kernels of the explicit MHD step.
 //
 // stage_kernel: one SSP-RK stage (Sect. 2.9) fused into one launch.  A block
-// owns a 14 x 14 column tile of the x-y plane and a segment of z planes; its
-// 16 x 16 threads hold one cell column each (the outer ring is the halo of
-// the three-cell reconstruction stencil, plus 64 ring cells two columns out
-// that only feed the x/y stencils).  The block marches up the segment; per
-// plane k it
-//   P1  converts plane k+2 to primitive deviations (EOS included) and stages
-//       it in LDS (two plane buffers), reconstructs cell k+1 of its own
-//       column along z and solves the z-face k+1/2, and reconstructs cell
-//       k+1 along x and y from the staged plane (one slope per cell and
-//       direction; the upper x value reaches the next lane by a shuffle,
-//       the upper y value goes through LDS),
-//   P2  solves the Riemann problems of the x- and y-faces of plane k+1,
-//   P3  updates the cells of plane k, accumulates the x/y flux divergence of
-//       plane k+1 and computes the Contact-CT edge EMFs E_z(k+1), E_x and
-//       E_y(k+1/2),
-//   P4  updates the faces B_x(k) and B_y(k); B_z(k+1/2), which needs the
-//       E_x(k+1/2) of the row above from P3, is updated in the next plane
-//       after its first barrier (two barriers per plane, after P1 and P2).
-// Neighbour exchanges inside a 16-lane row use lane shuffles; exchanges
-// across rows use small LDS arrays.  Fluxes and EMFs on tile borders are
-// recomputed by both neighbouring blocks from identical inputs with the
-// same code, so every face and edge value is single-valued (div B stays at
-// round-off) without atomics or a global EMF array.
+// marches up a segment of z planes of a 14 x 14 column tile, with a ring of
+// halo columns around it for the three-cell stencils: 16 x 16 columns, plus
+// 64 ring cells two columns out that only feed the x/y stencils.  Its waves
+// have one role each and work on different planes of the march at the same
+// time; what one computes at a step the others read at the next, so a step
+// needs one barrier.  At step i
+//   the column waves turn plane i into primitive deviations (EOS included),
+//     stage them in LDS, reconstruct cell i-1 of their column along z, solve
+//     the z-face between cells i-2 and i-1 and update the cells of plane i-2;
+//   the x-face waves compute the Contact-CT edges E_y on the z-face below
+//     plane i-2, update B_x and B_z of plane i-3 and B_y of plane i-4, and
+//     reconstruct and solve the x-faces of plane i-1;
+//   the y-face waves compute the edges E_x on the z-face below plane i-2 and
+//     E_z of plane i-2, convert the ring cells of plane i, and reconstruct
+//     and solve the y-faces of plane i-1.  Their lanes run along y, so that
+//     the y neighbour is the next lane, as the x neighbour is in the others.
+// In FP32 the x- and y-face work is done by the same waves, one after the
+// other.  Neighbour exchanges inside a 16-lane row use lane shuffles, the
+// others go through LDS.  Fluxes and EMFs on tile borders are recomputed by
+// both neighbouring blocks from identical inputs with the same code, so every
+// face and edge value is single-valued (div B stays at round-off) without
+// atomics or a global EMF array.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -57,25 +56,27 @@ __device__ __forceinline__ double from_right(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// z plane or face q of a periodic z with n planes, -2 <= q <= n + 1 (also
+// for n = 1: two steps of n reach the range; a division would cost more)
+__device__ __forceinline__ int zwrap(int q, int n) {
+  if (q < 0) q += n;
+  if (q < 0) q += n;
+  if (q >= n) q -= n;
+  if (q >= n) q -= n;
+  return q;
+}
 // z plane q -> stored plane and mirror flag (reflecting walls)
 __device__ __forceinline__ int zsource(const Phys &ph, int q, int &mirror) {
   mirror = 0;
   if (q >= 0 && q < ph.nz) return q;
-  if (!ph.reflect) return wrapi(q, ph.nz);
+  if (!ph.reflect) return zwrap(q, ph.nz);
   mirror = 1;
   return q < 0 ? -1 - q : 2 * ph.nz - 1 - q;
 }
 // z face index f (0..nz for walls) -> stored face
 __device__ __forceinline__ int zface(const Phys &ph, int f) {
-  return ph.reflect ? f : wrapi(f, ph.nz);
+  return ph.reflect ? f : zwrap(f, ph.nz);
 }
-
-struct CellLoad {
-  double u[5];
-  double b[3];
-  double bxl, byl;  // lower x / y faces of the cell (normal fields)
-  double tg;
-};
 
 // Element access through a plane's address and a lane's column.  The plane
 // address (array + field + plane) must be the same for every lane of the
@@ -119,53 +120,9 @@ __device__ __forceinline__ ColOff col_off(const Phys &ph, int gi, int gip, int g
           (uint32_t)(((size_t)gjp * ph.nx + gi) * 8)};
 }
 
-__device__ __forceinline__ void load_cell(const Phys &ph, const StagePtrs &p, ColOff co,
-                                          int kk, int mirror, CellLoad &c) {
-  const size_t plane = (size_t)ph.nx * ph.ny;
-  const size_t n = plane * ph.nz;
-  const size_t pk = (size_t)kk * plane;
-  const int kp = ph.reflect ? kk + 1 : wrapi(kk + 1, ph.nz);
-  const uint32_t o = lane_off(co.c), ox = lane_off(co.xp), oy = lane_off(co.yp);
-#pragma unroll
-  for (int f = 0; f < 5; ++f) c.u[f] = plane_ld(p.Us + f * n + pk, o);
-  c.bxl = plane_ld(p.Bxs + pk, o);
-  c.byl = plane_ld(p.Bys + pk, o);
-  const double bxr = plane_ld(p.Bxs + pk, ox);
-  const double byr = plane_ld(p.Bys + pk, oy);
-  const double bzl = plane_ld(p.Bzs + pk, o);
-  const double bzr = plane_ld(p.Bzs + (size_t)kp * plane, o);
-  c.b[0] = 0.5 * (c.bxl + bxr);
-  c.b[1] = 0.5 * (c.byl + byr);
-  c.b[2] = 0.5 * (bzl + bzr);
-  c.tg = p.Tin ? plane_ld(p.Tin + pk, lane_off(co.c)) : 0.0;
-  (void)mirror;
-}
-
 template <typename R, bool GR>
 struct Cfg {
   static constexpr int NF = GR ? 10 : 8;  // cell fields kept per cell
-};
-
-// primitive deviations of one cell, as R, with the mirror image applied
-template <typename R, bool GR>
-__device__ __forceinline__ void prim_cell(const Phys &ph, const CellLoad &c,
-                                          const double bg[4], int mirror, R *w,
-                                          PrimOut &o, int maxit = -1) {
-  cons2prim<GR>(ph, c.u, c.b, c.tg, bg, o, maxit);
-  constexpr int NF = Cfg<R, GR>::NF;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) w[f] = (R)o.w[f];
-  if (mirror) {
-    w[Q_VZ] = -w[Q_VZ];
-    w[Q_BZ] = -w[Q_BZ];
-  }
-}
-
-// Number of reconstructed fields per face: rho, v_n, v_t1, v_t2, P, B_t1, B_t2
-// (+ gamma_e, gamma_c for the gas+radiation EOS).
-template <bool GR>
-struct NFS_ {
-  static constexpr int v = GR ? 9 : 7;
 };
 
 // Reconstruction of one cell along `axis` (0 x, 1 y, 2 z) from its two
@@ -227,40 +184,6 @@ __device__ __forceinline__ Side<R> side_from_left(const Side<R> &s) {
   return o;
 }
 
-template <typename R, bool GR>
-__device__ __forceinline__ void side_store(R (*buf)[NTHREADS], int t, const Side<R> &s) {
-  buf[0][t] = s.drho;
-  buf[1][t] = s.vn;
-  buf[2][t] = s.v1;
-  buf[3][t] = s.v2;
-  buf[4][t] = s.dp;
-  buf[5][t] = s.b1;
-  buf[6][t] = s.b2;
-  if (GR) {
-    buf[7][t] = s.dge;
-    buf[8][t] = s.dgc;
-  }
-}
-
-template <typename R, bool GR>
-__device__ __forceinline__ Side<R> side_load(R (*buf)[NTHREADS], int t) {
-  Side<R> s;
-  s.drho = buf[0][t];
-  s.vn = buf[1][t];
-  s.v1 = buf[2][t];
-  s.v2 = buf[3][t];
-  s.dp = buf[4][t];
-  s.b1 = buf[5][t];
-  s.b2 = buf[6][t];
-  if (GR) {
-    s.dge = buf[7][t];
-    s.dgc = buf[8][t];
-  } else {
-    s.dge = s.dgc = R(0);
-  }
-  return s;
-}
-
 // face flux -> conserved order (rho, m_x, m_y, m_z, E)
 template <typename R>
 __device__ __forceinline__ void to_cons(int axis, const R F[7], R out[5]) {
@@ -284,7 +207,7 @@ struct StageArgs {
   Phys ph;
   StagePtrs p;
   double ca, cb, cc, dt_host;  // U^(s+1) = cb U^(s) + ca U^n - cc dt (div F - S)(U^(s))
-  int zseg;                    // planes per z segment
+  int tiles, full, share;      // the split of the work over the blocks (see the kernel)
 };
 
 // The stage's arguments read again from the argument segment, as a view
@@ -302,501 +225,800 @@ __device__ __forceinline__ const StageArgs &stage_args_view() {
   return *(const StageArgs *)a;
 }
 
-// XF: the optional features of a stage (forcing modes, shock-flattening
-// flags, species mass fluxes); the variant without them carries none of
-// their code, pointers or registers.
+#ifndef BZCOL
+#define BZCOL (sizeof(R) == 4)
+#endif
+#ifndef BZCOL
+#define BZCOL false
+#endif
+#ifndef LATEDEF
+#define LATEDEF (!GR)
+#endif
+#ifndef BZCOL
+#define BZCOL false
+#endif
+#ifndef LATEDEF
+#define LATEDEF false
+#endif
+#ifndef RINGFIRST
+#define RINGFIRST GR
+#endif
+#ifndef BZCOL
+#define BZCOL false
+#endif
+// Threads of a stage block: the columns' four waves and, in FP64, four each
+// for the x-faces and the y-faces, in FP32 four for both.  The split is by
+// registers: one wave that does all of a column needs 382 of them in FP64
+// (one wave per SIMD, every latency exposed), a third of it 165 (three waves
+// per SIMD, no value spilled); in FP32 a half fits 128 (two blocks of two
+// waves per SIMD), a third would have to fit 80 for two blocks and spills.
+// 256^3 stratified box per launch, one wave per column -> split: FP64 3.07 ->
+// 1.95 ms (the launch's 770 M vector instructions take 1.3 ms to issue),
+// 250 x 250 x 310 in FP32 1.81 -> 1.59 ms.
+template <typename R>
+constexpr int stage_threads() {
+  return sizeof(R) == 8 ? 3 * NTHREADS : 2 * NTHREADS;
+}
+
+// One block of stage_kernel in LDS.  Planes are held by parity: a plane
+// written during one step of the march is read during the next one, on the
+// other side of that step's barrier, while the next plane goes to the other
+// half.
+constexpr int LW = TT + 2;  // staged plane edge: columns -2 .. 15
+constexpr int LP = LW * LW;
+// exchanged face and edge values: 16 x 16 with an odd pitch (the y-face
+// waves walk a plane column by column) and one row and column of margin
+// below, so that a lower neighbour's index is in the array for every lane; an
+// upper neighbour's index past the last row (a halo lane's, whose value is
+// not used) falls into the next plane or the margin after the last one
+constexpr int EP = TT + 1;
+constexpr int EN = EP * (TT + 1);
 template <typename R, bool GR, bool XF>
-__global__ __launch_bounds__(NTHREADS) void stage_kernel(StageArgs args) {
-  const Phys &ph = args.ph;
-  const StagePtrs &p = args.p;
-  const double cc = args.cc, dt_host = args.dt_host;
-  const int zseg = args.zseg;
-  static_assert(sizeof(MlpLds) % 16 == 0, "MlpLds is copied in 16-byte words");
-  constexpr int NF = Cfg<R, GR>::NF;
-  // FP64 runs one wave per SIMD (register-bound): it has the registers to
-  // hold the next plane's cell data while it works on the current one
-  constexpr bool PREFETCH = sizeof(R) == 8;
-  // the ring cells' data too, except in the gas + radiation variant (its
-  // Newton iteration leaves the loads time to arrive; 1 % faster without)
-  constexpr bool RING_PREFETCH = PREFETCH && !GR;
-  constexpr int NS = NFS_<GR>::v;
-  constexpr int LW = TT + 2;  // LDS plane edge: columns -2 .. 15
-  constexpr int LP = LW * LW;
-  __shared__ R sW[2][NF][LP];       // cell planes by parity
-  __shared__ R sYR[NS][NTHREADS];   // upper y-face states of plane k+1
-  __shared__ R sYF[5][NTHREADS];    // y-face conserved flux
-  __shared__ R sXE[2][NTHREADS];    // x-face E_z, mass flux
-  __shared__ R sZE[2][NTHREADS];    // z-face E_x, mass flux
-  __shared__ R sRX[2][NTHREADS];    // cell reference E_x, planes by parity
-  __shared__ R sRZ[NTHREADS];       // cell reference E_z of plane k+1
-  __shared__ R sEZ[2][NTHREADS];    // edge E_z, planes by parity
-  __shared__ R sEX[NTHREADS];       // edge E_x(k+1/2)
-  __shared__ int sFL[NTHREADS];     // flattening flag of cell k+1
+struct StageLds {
+  static constexpr int NF = Cfg<R, GR>::NF;
+  R w[2][NF][LP];           // cell primitives (deviations)
+  R bx[2][EN], by[2][EN];   // fields on the lower x and y faces
+  R fx[2][5][EN];           // x-face conserved flux
+  R fy[2][5][EN];           // y-face conserved flux
+  R xez[2][EN];             // x-face E_z
+  R yez[2][EN];             // y-face E_z
+  R zex[2][EN], zey[2][EN]; // z-face E_x, E_y
+  R zm[2][EN];              // z-face mass flux
+  R rz[2][EN];              // cell reference E_z
+  R ex[2][EN], ez[2][EN];   // edge E_x, E_z
+  R margin[EP];
+  // rows of the launch's table (see StagePtrs) of planes i-3 .. i+1: uniform
+  // per plane, so every read is a broadcast
+  double tab[8][TAB_N];
+  uint8_t fl[XF ? 2 : 1][XF ? EN : 1];         // flattening flags
+  unsigned long long nst[GR ? 3 : 1][NTHREADS / 64];
+};
 
-  const int tid = threadIdx.x;
-  const int tx = tid % TT, ty = tid / TT;
-  const int ci = tx - 1, cj = ty - 1;
-  // each XCD works through a contiguous run of tiles (x fastest, then y,
-  // then z segment), so neighbouring tiles share its L2
-  const int ntx = (ph.nx + TB - 1) / TB, nty = (ph.ny + TB - 1) / TB;
-  const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
-  const int btx = lb % ntx, bty = (lb / ntx) % nty, bsz = lb / (ntx * nty);
-  const int X0 = btx * TB, Y0 = bty * TB;
-  const int z0 = bsz * zseg;
-  const int z1 = min(z0 + zseg, ph.nz);
-  const int gx = X0 + ci, gy = Y0 + cj;
-  const int gi = wrapi(gx, ph.nx), gip = wrapi(gx + 1, ph.nx);
-  const int gj = wrapi(gy, ph.ny), gjp = wrapi(gy + 1, ph.ny);
-  const bool owner = ci >= 0 && ci < TB && cj >= 0 && cj < TB && gx < ph.nx && gy < ph.ny;
+// A segment of the block's work, planes z0 .. z1-1 of one column tile, and a
+// thread's column in it.  What follows from the thread's number is worked
+// out again at each step: held over the march it would cost registers the
+// face solves need, and a value spilled to scratch is read back through the
+// queue of the global loads, behind every load in flight.
+struct StageTile {
+  int z0, z1;
+  int tid;         // thread of the role, 0 .. 255
+  bool owner;      // the block updates this column
+  bool xedge, yedge;  // the column's upper x / y face wraps
+  uint32_t col;    // byte offset of the column in a plane
+};
+struct StageIdx {
+  int w, e;        // index of the column in a staged plane, in an exchanged plane
+};
+__device__ __forceinline__ int restate(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+// lanes of a row along x: column (tid % 16 - 1, tid / 16 - 1)
+__device__ __forceinline__ StageIdx idx_rows(int tid) {
+  const int q = restate(tid), r = q / TT;
+  return {q + 2 * r + LW + 1, q + r + EP + 1};
+}
+// lanes of a row along y: column (tid / 16 - 1, tid % 16 - 1)
+__device__ __forceinline__ StageIdx idx_cols(int tid) {
+  const int q = restate(tid), r = q / TT, l = q % TT;
+  return {l * LW + r + LW + 1, l * EP + r + EP + 1};
+}
+__device__ __forceinline__ ColOff tile_off(const Phys &ph, const StageTile &t) {
+  const uint32_t row = (uint32_t)ph.nx * 8;
+  return {t.col, t.xedge ? t.col - (row - 8) : t.col + 8,
+          t.yedge ? t.col - row * (uint32_t)(ph.ny - 1) : t.col + row};
+}
 
-  // Background profile (and heating) of the planes this block touches,
-  // staged once: cell planes q = z0-2 .. z1+1 (mirror / wrap applied) and
-  // z faces z0 .. z1.  Uniform per plane, so every read is a broadcast.
-  __shared__ double sBc[5][ZSEG_MAX + 4];  // rho, P, gamma_e, gamma_c, heat
-  __shared__ double sBf[4][ZSEG_MAX + 1];
-  // forcing from Fourier modes: the z basis of the same planes, and this
-  // thread's column coefficients (3 components x FZB), as R
-  __shared__ double sZB[XF ? FZB : 1][ZSEG_MAX + 4];
-  __shared__ R sFC[XF ? 3 * FZB : 1][NTHREADS];
+// A value that is not set on every path below: the register starts a new
+// life here (no instruction), so that its old value does not stay live up to
+// this point.
+template <typename T>
+__device__ __forceinline__ void renew(T &x) {
+  asm("" : "=v"(x));
+}
+template <typename R, bool GR>
+__device__ __forceinline__ void renew_side(Side<R> &s) {
+  renew(s.drho);
+  renew(s.vn);
+  renew(s.v1);
+  renew(s.v2);
+  renew(s.dp);
+  renew(s.b1);
+  renew(s.b2);
+  if (GR) {
+    renew(s.dge);
+    renew(s.dgc);
+  }
+}
+
+// Entry `lane` of the table rows of plane i (mirror / wrap applied): the
+// cell's entries, then those of its lower face.
+__device__ __forceinline__ double table_request(const Phys &ph, const StagePtrs &p, int i,
+                                                int lane) {
+  int mir;
+  const int kk = zsource(ph, i, mir);
+  const int fk = ph.reflect ? max(0, min(i, ph.nz)) : zwrap(i, ph.nz);
+  // the two rows are at most two apart: one base for both
+  const int k0 = min(kk, fk);
+  double v;
+  renew(v);
+  if (lane < TAB_N)
+    v = plane_ld(p.table + (size_t)k0 * TAB_N,
+                 lane_off((uint32_t)(((lane < TAB_FACE ? kk : fk) - k0) * TAB_N + lane) * 8));
+  return v;
+}
+
+// What a wave carries from one step of the march to the next: reconstructed
+// states, fluxes and EMFs (st, listed at each role) and the global values
+// requested at the end of a step for the next one.
+constexpr int ST_N = 14, PRE_N = 12;  // column waves
+constexpr int XST_N = 10, XPRE_N = 6, YST_N = 8;  // face waves
+
+// raw values of one cell: U, the six faces, the temperature guess
+__device__ __forceinline__ void request_cell(const Phys &ph, const StagePtrs &p, ColOff co, int kk,
+                                             double *pre) {
   const size_t plane = (size_t)ph.nx * ph.ny;
-  const size_t colq = (size_t)gj * ph.nx + gi;
-  {
-    const int nq = z1 - z0 + 4, nf = z1 - z0 + 1;
-    for (int i = threadIdx.x; i < 5 * nq; i += NTHREADS) {
-      const int f = i / nq, j = i - f * nq;
-      int mir;
-      const int kk = zsource(ph, z0 - 2 + j, mir);
-      sBc[f][j] = f < 4 ? p.bg_cc[f * ph.nz + kk] : (p.heat ? p.heat[kk] : 0.0);
-    }
-    for (int i = threadIdx.x; i < 4 * nf; i += NTHREADS) {
-      const int f = i / nf, j = i - f * nf;
-      sBf[f][j] = p.bg_fz[f * ph.nzf + zface(ph, z0 + j)];
-    }
-    if (XF && p.fcoef) {
-      for (int i = threadIdx.x; i < FZB * nq; i += NTHREADS) {
-        const int f = i / nq, j = i - f * nq;
-        int mir;
-        const int kk = zsource(ph, z0 - 2 + j, mir);
-        sZB[f][j] = p.fzb[f * ph.nz + kk];
-      }
+  const size_t n = plane * ph.nz;
+  const size_t pk = (size_t)kk * plane;
+  const int kp = ph.reflect ? kk + 1 : zwrap(kk + 1, ph.nz);
+  const uint32_t o = lane_off(co.c), ox = lane_off(co.xp), oy = lane_off(co.yp);
 #pragma unroll
-      for (int d = 0; d < 3 * FZB; ++d) sFC[d][threadIdx.x] = (R)p.fcoef[d * plane + colq];
-    }
+  for (int f = 0; f < 5; ++f) pre[f] = plane_ld(p.Us + f * n + pk, o);
+  pre[5] = plane_ld(p.Bxs + pk, o);
+  pre[6] = plane_ld(p.Bys + pk, o);
+  pre[7] = plane_ld(p.Bxs + pk, ox);
+  pre[8] = plane_ld(p.Bys + pk, oy);
+  pre[9] = plane_ld(p.Bzs + pk, o);
+  pre[10] = plane_ld(p.Bzs + (size_t)kp * plane, o);
+  pre[11] = p.Tin ? plane_ld(p.Tin + pk, lane_off(co.c)) : 0.0;
+}
+
+// primitive deviations of the requested cell, as R, with the mirror image
+// applied
+template <typename R, bool GR>
+__device__ __forceinline__ void prim_cell(const Phys &ph, const double *pre, const double bg[4],
+                                          int mirror, R *w, PrimOut &o, int maxit) {
+  const double b[3] = {0.5 * (pre[5] + pre[7]), 0.5 * (pre[6] + pre[8]), 0.5 * (pre[9] + pre[10])};
+  cons2prim<GR>(ph, pre, b, pre[11], bg, o, maxit);
+  constexpr int NF = Cfg<R, GR>::NF;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) w[f] = (R)o.w[f];
+  if (mirror) {
+    w[Q_VZ] = -w[Q_VZ];
+    w[Q_BZ] = -w[Q_BZ];
   }
-  __syncthreads();
+}
 
-  // ring cells two columns outside the tile (x/y stencils only): the first
-  // 16 lanes of each wave take one of the four sides, so that every wave
-  // carries the same extra work into the first barrier
-  const int lane = tid & 63, wv = tid >> 6;
-  const bool ring = lane < 16;
-  int rci = 0, rcj = 0;
-  if (wv == 0) {
-    rci = -2; rcj = lane - 1;
-  } else if (wv == 1) {
-    rci = TT - 1; rcj = lane - 1;
-  } else if (wv == 2) {
-    rci = lane - 1; rcj = -2;
-  } else {
-    rci = lane - 1; rcj = TT - 1;
+// Ring cells two columns outside the tile (they only feed the x/y
+// stencils): the first 16 lanes of each of four waves take one of the four
+// sides, so that every SIMD carries the same extra work.
+struct RingCell {
+  bool on;
+  int w;       // index in a staged plane
+  ColOff co;
+};
+__device__ __forceinline__ RingCell ring_cell(const Phys &ph, int X0, int Y0, int tid) {
+  const int wv = tid >> 6, lane = tid & 63;
+  int ci = lane - 1, cj = lane - 1;
+  if (wv == 0) ci = -2;
+  if (wv == 1) ci = TT - 1;
+  if (wv == 2) cj = -2;
+  if (wv == 3) cj = TT - 1;
+  return {lane < 16, (cj + 2) * LW + (ci + 2),
+          col_off(ph, wrapi(X0 + ci, ph.nx), wrapi(X0 + ci + 1, ph.nx), wrapi(Y0 + cj, ph.ny),
+                  wrapi(Y0 + cj + 1, ph.ny))};
+}
+
+// the requested ring cell of plane i to the staged plane
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void ring_step(const StageArgs &A, StageLds<R, GR, XF> &S,
+                                          const RingCell &rc, int i, const double *pre, int &bad) {
+  constexpr int NF = Cfg<R, GR>::NF;
+  int mir;
+  (void)zsource(A.ph, i, mir);
+  if (rc.on) {
+    const double *bg = S.tab[i & 7];
+    PrimOut o;
+    R Wr[NF];
+    prim_cell<R, GR>(A.ph, pre, bg, mir, Wr, o, A.p.newton_cap);
+    bad |= o.bad;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) S.w[i & 1][f][rc.w] = Wr[f];
   }
-  const int rgi = wrapi(X0 + rci, ph.nx), rgip = wrapi(X0 + rci + 1, ph.nx);
-  const int rgj = wrapi(Y0 + rcj, ph.ny), rgjp = wrapi(Y0 + rcj + 1, ph.ny);
-  const ColOff cofs = col_off(ph, gi, gip, gj, gjp), rofs = col_off(ph, rgi, rgip, rgj, rgjp);
-  const int lw_own = (cj + 2) * LW + (ci + 2);
-  const int lw_ring = (rcj + 2) * LW + (rci + 2);
-  const int tdn = tid >= TT ? tid - TT : tid;            // (ci, cj-1)
-  const int tdl = tid >= TT + 1 ? tid - TT - 1 : tid;    // (ci-1, cj-1)
-  const int tup = tid + TT < NTHREADS ? tid + TT : tid;  // (ci, cj+1)
+}
+// ... and the request of plane i
+__device__ __forceinline__ void ring_request(const Phys &ph, const StagePtrs &p, const RingCell &rc,
+                                             int i, double (&pre)[PRE_N]) {
+  int mir;
+  const int kk = zsource(ph, i, mir);
+#pragma unroll
+  for (int f = 0; f < PRE_N; ++f) renew(pre[f]);
+  if (rc.on) request_cell(ph, p, rc.co, kk, pre);
+}
 
-  const double dt = p.dt_dev ? *p.dt_dev : dt_host;
-  const double cdt = cc * dt;
-  const R gam = (R)ph.gamma, igm1 = (R)ph.igm1;
-  const R mcut = (R)ph.mach_cut, imcut = (R)ph.imach_cut;
-  const bool pph = ph.recon == MHD_RECON_PPH;
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ double uniform(double x) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(x)));
+}
 
-  // own column state carried along z
-  R Wc[NF];        // cell k+1
-  Side<R> topk{};  // upper z-face state of cell k (L state of face k+1/2)
-  R bxf_c = 0, byf_c = 0;  // normal fields on the lower x / y face, plane k+1
-  double acc[5] = {0, 0, 0, 0, 0};  // x/y flux divergence of plane k
-  R fzp[5] = {0, 0, 0, 0, 0};       // z-face conserved flux at k-1/2
-  R ex_prev = 0, ey_prev = 0;       // own edges E_x, E_y at k-1/2
-  R ez_cur = 0;                     // own edge E_z at plane k
-  double bzf_prev = 0.0, bz0_prev = 0.0;  // B_z^(s), B_z^n of the face k+1/2 of the previous plane
-  R xf_ey_prev = 0, xf_m_prev = 0;  // own x-face E_y and mass flux, plane k
-  R yf_ex_prev = 0, yf_m_prev = 0;  // own y-face E_x and mass flux, plane k
-  R rx_prev = 0, ry_prev = 0;       // own cell reference E_x, E_y, plane k
-  // shock-flattening flags of the own column's cells k and k+1 (Sect. 2.7):
-  // a flagged cell is reconstructed with van Leer, and every face it
-  // touches takes the HLL flux
-  int fk = 0, fc = 0;
-  unsigned long long nit = 0, nmax = 0, nfb = 0;
+// Error bits and Newton statistics of a thread.
+struct StageCount {
+  unsigned it = 0, mx = 0, fb = 0;
   int bad = 0;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) Wc[f] = R(0);
+};
 
-  CellLoad pc{}, prc{};  // prefetched cell data of the next P1 plane
-  if (PREFETCH) {
+// Column waves, step i: primitives of plane i, the z-face between cells i-2
+// and i-1, the update of the cells of plane i-2.
+// st: 0..8 upper z-face state of cell i-2, 9..13 z-face flux of the face i-2.
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, GR, XF> &S,
+                                             const StageTile &t, double cdt, StageCount &n) {
+  constexpr int NF = Cfg<R, GR>::NF;
+  // FP32 with the optional features: the update is finished at the top of the
+  // next step, so its values arrive over the barrier and are not live beside
+  // the forcing (26 spilled registers instead of 37; turbulence box at 384^3
+  // 36.9 -> 34.1 ms for two steps); the others lose 0 to 4 % that way
+  constexpr bool LATE = sizeof(R) == 4 && XF;
+  const int z0 = t.z0, z1 = t.z1;
+  R st[ST_N];
+#pragma unroll
+  for (int f = 0; f < ST_N; ++f) st[f] = R(0);
+  double pre[PRE_N];
+  double us[5], u0[5], r[5];  // the update in progress: U^(s), U^n, divergence
+#pragma unroll
+  for (int f = 0; f < 5; ++f) us[f] = u0[f] = r[f] = 0.0;
+  int fk = 0, fc = 0;  // flags of the column's cells i-2 and i-1
+  {
+    const Phys &ph = args.ph;
     int mir0;
     const int k0 = zsource(ph, z0 - 2, mir0);
-    load_cell(ph, p, cofs, k0, mir0, pc);
-    if (RING_PREFETCH && ring) load_cell(ph, p, rofs, k0, mir0, prc);
+    request_cell(ph, args.p, tile_off(ph, t), k0, pre);
   }
-  for (int k = z0 - 4; k < z1; ++k) {
-    // this plane's view of the arguments (shadows the kernel's own names);
-    // FP32 variants only: the FP64 kernel, one wave per SIMD and bound by
-    // latency, ran no faster with the scalar loads (the gas+radiation
-    // variant 0.7 % slower)
-    const StageArgs &A = sizeof(R) == 4 ? stage_args_view() : args;
+  // coefficients of the forcing of the column
+  R fco[XF ? 3 * FZB : 1];
+  if (XF && args.p.fcoef) {
+    const size_t plane = (size_t)args.ph.nx * args.ph.ny;
+#pragma unroll
+    for (int d = 0; d < 3 * FZB; ++d)
+      fco[XF ? d : 0] = plane_ld((const R *)args.p.fcoef + d * plane, lane_off(t.col / (8 / sizeof(R))));
+  }
+  for (int i = z0 - 2; i <= z1 + 3; ++i) {
+    const StageArgs &A = stage_args_view();
     const Phys &ph = A.ph;
     const StagePtrs &p = A.p;
     const double ca = A.ca, cb = A.cb;
     const size_t plane = (size_t)ph.nx * ph.ny;
     const size_t ncell = plane * ph.nz;
-    // every global value P3 and P4 read, requested together at the top of
-    // the plane so that the latency overlaps P1 and P2
-    const bool upd = k >= z0 && owner;
-    const bool updz = k >= z0 - 1 && k + 1 < z1 && owner && !(ph.reflect && k + 1 == 0);
-    const bool base = ca != 0.0;
-    double us[5] = {0, 0, 0, 0, 0}, u0[5] = {0, 0, 0, 0, 0};
-    double bxs = 0.0, bys = 0.0, bx0 = 0.0, by0 = 0.0, bz0 = 0.0;
-    const size_t pqc = (size_t)(k > 0 ? k : 0) * plane;
-    const size_t pqf = (size_t)(k + 1 > 0 ? k + 1 : 0) * plane;
-    if (upd) {
-      const uint32_t o = lane_off(cofs.c);
+    const int b = i & 1, pb = b ^ 1;
+    // finishes the update of the cells of plane k
+    auto finish = [&](int k) {
+      const double *tab = S.tab[k & 7];
+      // sources S - S_hat: gravity on the density deviation, rho g.v,
+      // heating, forcing (Sect. 2.1, eq. wb2)
+      double s1 = 0.0, s2 = 0.0, s3 = (us[0] - tab[0]) * ph.gz;
+      double s4 = us[3] * ph.gz + tab[4];
+      if (XF && p.fcoef) {
+        // the forcing of this cell from its column's coefficients
+        double fo[3];
 #pragma unroll
-      for (int f = 0; f < 5; ++f) us[f] = plane_ld(p.Us + f * ncell + pqc, o);
-      bxs = plane_ld(p.Bxs + pqc, o);
-      bys = plane_ld(p.Bys + pqc, o);
-    }
-    if (upd && base) {
-      const uint32_t o = lane_off(cofs.c);
+        for (int c3 = 0; c3 < 3; ++c3) {
+          double f = 0.0;
 #pragma unroll
-      for (int f = 0; f < 5; ++f) u0[f] = plane_ld(p.U0 + f * ncell + pqc, o);
-      bx0 = plane_ld(p.Bx0 + pqc, o);
-      by0 = plane_ld(p.By0 + pqc, o);
-    }
-    if (updz && base) bz0 = plane_ld(p.Bz0 + pqf, lane_off(cofs.c));
-    // ---------------- P1 ------------------------------------------------
-    // primitives of plane k+2 (staged in LDS), z reconstruction of cell
-    // k+1 and the z-face k+1/2, x/y reconstruction of cell k+1
-    R Wn[NF];
-    R bxf_n, byf_n;
-    double bzf = 0.0;  // B_z on the z-face k+1/2 (read again by P4)
-    R fzc[5] = {0, 0, 0, 0, 0};
-    R zf_ey = 0, zf_ex = 0, zf_m = 0;
-    Side<R> xl{}, xll{}, yl{};
-    R rx = 0, ry = 0, rz = 0;
-    int fn = 0;  // flag of cell k+2 (a mirror image carries its source's)
-    {
-      const int q = k + 2;
-      int mir;
-      const int kk = zsource(ph, q, mir);
-      if (XF && p.flat) fn = plane_ld(p.flat + (size_t)kk * plane, lane_off(cofs.c >> 3));
-      R *sWn = &sW[q & 1][0][0];
-      CellLoad c, rc;
-      if (PREFETCH) {
-        // plane q arrived during the previous plane; request plane q+1
-        c = pc;
-        if (RING_PREFETCH) rc = prc;
-        if (k + 1 < z1) {
-          int mirn;
-          const int kn = zsource(ph, q + 1, mirn);
-          load_cell(ph, p, cofs, kn, mirn, pc);
-          if (RING_PREFETCH && ring) load_cell(ph, p, rofs, kn, mirn, prc);
+          for (int d = 0; d < FZB; ++d)
+            f += (double)fco[XF ? c3 * FZB + d : 0] * tab[5 + d];
+          fo[c3] = f;
         }
-      } else {
-        load_cell(ph, p, cofs, kk, mir, c);
+        s1 += us[0] * fo[0];
+        s2 += us[0] * fo[1];
+        s3 += us[0] * fo[2];
+        s4 += us[1] * fo[0] + us[2] * fo[1] + us[3] * fo[2];
       }
-      const int maxit = p.newton_cap;
-      const int jq = q - (z0 - 2);
-      const double bgq[4] = {sBc[0][jq], sBc[1][jq], sBc[2][jq], sBc[3][jq]};
-      {
-        PrimOut o;
-        prim_cell<R, GR>(ph, c, bgq, mir, Wn, o, maxit);
-        bxf_n = (R)c.bxl;
-        byf_n = (R)c.byl;
-        if (GR) {
-          if (owner && q >= z0 && q < z1) {
-            if (p.Tout) plane_st(p.Tout + (size_t)kk * plane, lane_off(cofs.c), o.T);
-            nit += o.iters;
-            nmax = o.iters > nmax ? o.iters : nmax;
-            nfb += o.fallback;
-          }
-        }
-        bad |= o.bad;
-      }
-      if (ring) {
-        if (!RING_PREFETCH) load_cell(ph, p, rofs, kk, mir, rc);
-        PrimOut ro;
-        R Wr[NF];
-        prim_cell<R, GR>(ph, rc, bgq, mir, Wr, ro, maxit);
-        bad |= ro.bad;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) sWn[f * LP + lw_ring] = Wr[f];
-      }
-      // own cell k sits in the slot the new plane goes to; only this thread
-      // reads or writes that slot
-      R Wm[NF];
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        Wm[f] = sWn[f * LP + lw_own];
-        sWn[f * LP + lw_own] = Wn[f];
-      }
-      if (k >= z0 - 2) {
-        Side<R> botn, topn;
-        const bool pphc = pph && !(XF && fc);
-        recon_cell<R, GR>(2, Wm, Wc, Wn, botn, topn, pphc);
-        if (k >= z0 - 1) {
-          const int fzi = zface(ph, k + 1);
-          FaceBg<R> bgf;
-          const int jf = k + 1 - z0;
-          bgf.rho = (R)sBf[0][jf];
-          bgf.p = (R)sBf[1][jf];
-          bgf.ge = (R)sBf[2][jf];
-          bgf.gc = (R)sBf[3][jf];
-          bzf = plane_ld(p.Bzs + (size_t)fzi * plane, lane_off(cofs.c));
-          const R bzn = (R)bzf;
-          R fz[7];
-          face_flux<R, GR>(XF && (fk | fc) != 0, topk, botn, bzn, bgf, gam, igm1, ph.xi_mode,
-                           mcut, imcut, fz);
-          // mass flux for the species: the lower face of cell k+1 (and the
-          // top wall), written once, by the block that owns the cell
-          const int f = k + 1;
-          if (XF && p.mfz && owner && ((f >= z0 && f < z1) || (ph.reflect && f == ph.nz)))
-            plane_st(p.mfz + (size_t)f * plane, lane_off(cofs.c), (double)fz[0]);
-          to_cons<R>(2, fz, fzc);
-          zf_ey = -fz[5];  // z-face E_y = -F_z[B_x]
-          zf_ex = fz[6];   // z-face E_x = +F_z[B_y]
-          zf_m = fz[0];
-        }
-        topk = topn;
-        // x/y reconstruction of cell k+1 from the staged plane k+1
-        const R *sWc = &sW[(k + 1) & 1][0][0];
-        // neighbours at ci-1 >= -2 and cj-1 >= -2 are staged (ring cells
-        // included): the halo column ci = -1 supplies the L state of the
-        // tile's first x-face
-        R a[NF], b[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          a[f] = sWc[f * LP + lw_own - 1];
-          b[f] = sWc[f * LP + lw_own + 1];
-        }
-        Side<R> xh;
-        recon_cell<R, GR>(0, a, Wc, b, xl, xh, pphc);
-        xll = side_from_left<R>(xh);  // L state of the x-face ci-1/2
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          a[f] = sWc[f * LP + lw_own - LW];
-          b[f] = sWc[f * LP + lw_own + LW];
-        }
-        Side<R> yh;
-        recon_cell<R, GR>(1, a, Wc, b, yl, yh, pphc);
-        side_store<R, GR>(sYR, tid, yh);
-        if (XF) sFL[tid] = fc;
-        // cell reference EMF -(v x B) of plane k+1
-        rx = -(Wc[Q_VY] * Wc[Q_BZ] - Wc[Q_VZ] * Wc[Q_BY]);
-        ry = -(Wc[Q_VZ] * Wc[Q_BX] - Wc[Q_VX] * Wc[Q_BZ]);
-        rz = -(Wc[Q_VX] * Wc[Q_BY] - Wc[Q_VY] * Wc[Q_BX]);
-      }
-    }
-    __syncthreads();
-
-    // ---------------- B_z(k-1/2), the previous plane's z-face ------------
-    // its E_x neighbour (the row above) comes from that plane's P3, visible
-    // since the barrier above; the next write of sEX follows the barrier
-    // after P2
-    {
-      const R ey_r = from_right(ey_prev);
-      const bool updz_prev = k - 1 >= z0 - 1 && k < z1 && owner && !(ph.reflect && k == 0);
-      if (updz_prev) {
-        const double ex_u = (double)sEX[tup];
-        const double rbz = ((double)ey_r - (double)ey_prev) * ph.idx -
-                           (ex_u - (double)ex_prev) * ph.idy;
-        plane_st(p.Bzo + pqc, lane_off(cofs.c), cb * bzf_prev - cdt * rbz + ca * bz0_prev);
-      }
-    }
-
-    // ---------------- P2: x- and y-faces of plane k+1 --------------------
-    R fx[7], fy[7];
-#pragma unroll
-    for (int c = 0; c < 7; ++c) fx[c] = fy[c] = R(0);
-    if (k >= z0 - 2) {
-      const int jc = k + 1 - (z0 - 2);
-      FaceBg<R> bgc;
-      bgc.rho = (R)sBc[0][jc];
-      bgc.p = (R)sBc[1][jc];
-      bgc.ge = (R)sBc[2][jc];
-      bgc.gc = (R)sBc[3][jc];
-      const bool hx = XF && (fc | dpp_shr1(fc)) != 0;  // cells ci-1 and ci
-      face_flux<R, GR>(hx, xll, xl, bxf_c, bgc, gam, igm1, ph.xi_mode, mcut, imcut, fx);
-      const Side<R> yll = side_load<R, GR>(sYR, tdn);
-      const bool hy = XF && (fc | sFL[tdn]) != 0;  // cells cj-1 and cj
-      face_flux<R, GR>(hy, yll, yl, byf_c, bgc, gam, igm1, ph.xi_mode, mcut, imcut, fy);
-      R fyc[5];
-      to_cons<R>(1, fy, fyc);
-#pragma unroll
-      for (int f = 0; f < 5; ++f) sYF[f][tid] = fyc[f];
-      // mass fluxes for the species: the lower x and y faces of the owned
-      // cells of plane k+1
-      if (XF && p.mfx && owner && k + 1 >= z0 && k + 1 < z1) {
-        const size_t pf = (size_t)(k + 1) * plane;
-        const uint32_t o = lane_off(cofs.c);
-        plane_st(p.mfx + pf, o, (double)fx[0]);
-        plane_st(p.mfy + pf, o, (double)fy[0]);
-      }
-      sXE[0][tid] = -fx[5];  // x-face E_z = -F_x[B_y]
-      sXE[1][tid] = fx[0];
-      sZE[0][tid] = zf_ex;
-      sZE[1][tid] = zf_m;
-      sRX[(k + 1) & 1][tid] = rx;
-      sRZ[tid] = rz;
-    }
-    __syncthreads();
-
-    // ---------------- P3: cells of plane k, divergence, edge EMFs -------
-    R fxc[5];
-    to_cons<R>(0, fx, fxc);
-    R fxr[5];
-#pragma unroll
-    for (int f = 0; f < 5; ++f) fxr[f] = from_right(fxc[f]);
-    // neighbour data at ci-1 (same row)
-    const R yf_ez_l = from_left(fy[6]);  // y-face E_z = +F_y[B_x]
-    const R yf_m_l = from_left(fy[0]);
-    const R rz_l = from_left(rz);
-    const R zf_ey_l = from_left(zf_ey);
-    const R zf_m_l = from_left(zf_m);
-    const R ry_l = from_left(ry);
-    const R ry_prev_l = from_left(ry_prev);
-    R ex_new = 0, ey_new = 0, ez_new = 0;
-    if (k >= z0 - 1) {
-      // cells of plane k
-      if (upd) {
-        double r[5];
-#pragma unroll
-        for (int f = 0; f < 5; ++f) r[f] = acc[f] + ((double)fzc[f] - (double)fzp[f]) * ph.idz;
-        // sources S - S_hat: gravity on the density deviation, rho g.v,
-        // heating, forcing (Sect. 2.1, eq. wb2)
-        const int jk = k - (z0 - 2);
-        double s1 = 0.0, s2 = 0.0, s3 = (us[0] - sBc[0][jk]) * ph.gz;
-        double s4 = us[3] * ph.gz + sBc[4][jk];
-        if (XF && p.fcoef) {
-          // the forcing of this cell from its column's coefficients
-          double fo[3];
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            double f = 0.0;
-#pragma unroll
-            for (int d = 0; d < FZB; ++d) f += (double)sFC[c * FZB + d][tid] * sZB[d][jk];
-            fo[c] = f;
-          }
-          s1 += us[0] * fo[0];
-          s2 += us[0] * fo[1];
-          s3 += us[0] * fo[2];
-          s4 += us[1] * fo[0] + us[2] * fo[1] + us[3] * fo[2];
-        }
-        r[1] -= s1;
-        r[2] -= s2;
-        r[3] -= s3;
-        r[4] -= s4;
-        {
-          const uint32_t o = lane_off(cofs.c);
-#pragma unroll
-          for (int f = 0; f < 5; ++f)
-            plane_st(p.Uo + f * ncell + pqc, o, cb * us[f] - cdt * r[f] + ca * u0[f]);
-        }
-      }
-      // x/y divergence of plane k+1
-      R fyc[5];
-      to_cons<R>(1, fy, fyc);
+      r[1] -= s1;
+      r[2] -= s2;
+      r[3] -= s3;
+      r[4] -= s4;
+      const size_t pq = (size_t)k * plane;
+      const uint32_t o = lane_off(t.col);
 #pragma unroll
       for (int f = 0; f < 5; ++f)
-        acc[f] = ((double)fxr[f] - (double)fxc[f]) * ph.idx +
-                 ((double)sYF[f][tup] - (double)fyc[f]) * ph.idy;
-      // E_z at (ci-1/2, cj-1/2, k+1): a = x, b = y
-      ez_new = ct_edge<R>(-fx[5], sXE[0][tdn], fy[6], yf_ez_l, rz, rz_l, sRZ[tdn],
-                          sRZ[tdl], fx[0], sXE[1][tdn], fy[0], yf_m_l);
-      // E_x at (ci, cj-1/2, k+1/2): a = y (y-faces at planes k+1, k),
-      // b = z (z-faces at cj, cj-1)
-      const int s1 = (k + 1) & 1, s0 = k & 1;
-      ex_new = ct_edge<R>(-fy[5], yf_ex_prev, zf_ex, sZE[0][tdn], rx, sRX[s1][tdn], rx_prev,
-                          sRX[s0][tdn], fy[0], yf_m_prev, zf_m, sZE[1][tdn]);
-      // E_y at (ci-1/2, cj, k+1/2): a = z (z-faces at ci, ci-1), b = x
-      // (x-faces at planes k+1, k)
-      ey_new = ct_edge<R>(zf_ey, zf_ey_l, fx[6], xf_ey_prev, ry, ry_prev, ry_l, ry_prev_l,
-                          zf_m, zf_m_l, fx[0], xf_m_prev);
-      // a reflecting wall carries no tangential EMF
-      if (ph.reflect && (k + 1 == 0 || k + 1 == ph.nz)) {
-        ex_new = R(0);
-        ey_new = R(0);
+        plane_st(p.Uo + f * ncell + pq, o, cb * us[f] - cdt * r[f] + ca * u0[f]);
+    };
+    if (LATE && i >= z0 + 3 && i <= z1 + 2 && t.owner) finish(i - 3);
+    if (i <= z1 + 1) {
+      const StageIdx ix = idx_rows(t.tid);
+      const int w = ix.w, e = ix.e;
+      int mir;
+      const int kk = zsource(ph, i, mir);
+      int fn = 0;  // flag of cell i (a mirror image carries its source's)
+      if (XF && p.flat) fn = plane_ld(p.flat + (size_t)kk * plane, lane_off(t.col >> 3));
+      double bzf = 0.0;
+      if (i >= z0 + 1)
+        bzf = plane_ld(p.Bzs + (size_t)zface(ph, i - 1) * plane, lane_off(t.col));
+      // primitives of plane i, staged for the face waves
+      R Wn[NF];
+      {
+        const double *bg = S.tab[i & 7];
+        PrimOut o;
+        prim_cell<R, GR>(ph, pre, bg, mir, Wn, o, p.newton_cap);
+        S.bx[b][e] = (R)pre[5];
+        S.by[b][e] = (R)pre[6];
+        if (GR) {
+          if (t.owner && i >= z0 && i < z1) {
+            if (p.Tout) plane_st(p.Tout + (size_t)kk * plane, lane_off(t.col), o.T);
+            n.it += o.iters;
+            n.mx = (unsigned)o.iters > n.mx ? o.iters : n.mx;
+            n.fb += o.fallback;
+          }
+        }
+        n.bad |= o.bad;
       }
-      sEZ[(k + 1) & 1][tid] = ez_new;
-      sEX[tid] = ex_new;
-    }
-
-    // ---------------- P4: faces B_x(k), B_y(k) ---------------------------
-    // E_z of the row above at plane k comes from the previous plane's P3
-    const R ez_r = from_right(ez_cur);
-    if (upd) {
-      const double ez_u = (double)sEZ[k & 1][tup];
-      const double rbx = (ez_u - (double)ez_cur) * ph.idy -
-                         ((double)ey_new - (double)ey_prev) * ph.idz;
-      const double rby = ((double)ex_new - (double)ex_prev) * ph.idz -
-                         ((double)ez_r - (double)ez_cur) * ph.idx;
-      const uint32_t o = lane_off(cofs.c);
-      plane_st(p.Bxo + pqc, o, cb * bxs - cdt * rbx + ca * bx0);
-      plane_st(p.Byo + pqc, o, cb * bys - cdt * rby + ca * by0);
-    }
-    bzf_prev = bzf;
-    bz0_prev = bz0;
-
-    // ---------------- shift the pipeline --------------------------------
-    ez_cur = ez_new;
-    ex_prev = ex_new;
-    ey_prev = ey_new;
+      if (XF) S.fl[b][e] = (uint8_t)fn;
+      // own cells i-2 (its slot is the one plane i goes to; only this thread
+      // reads or writes that slot) and i-1
+      R Wm[NF], Wc[NF];
 #pragma unroll
-    for (int f = 0; f < 5; ++f) fzp[f] = fzc[f];
-    xf_ey_prev = fx[6];
-    xf_m_prev = fx[0];
-    yf_ex_prev = -fy[5];
-    yf_m_prev = fy[0];
-    rx_prev = rx;
-    ry_prev = ry;
+      for (int f = 0; f < NF; ++f) {
+        Wm[f] = S.w[b][f][w];
+        Wc[f] = S.w[pb][f][w];
+        S.w[b][f][w] = Wn[f];
+      }
+      Side<R> topn;  // upper z-face state of cell i-1
+      R fzc[5];
+      renew_side<R, GR>(topn);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) Wc[f] = Wn[f];
-    bxf_c = bxf_n;
-    byf_c = byf_n;
-    fk = fc;
-    fc = fn;
+      for (int f = 0; f < 5; ++f) renew(fzc[f]);
+      if (i >= z0) {
+        Side<R> botn;
+        recon_cell<R, GR>(2, Wm, Wc, Wn, botn, topn,
+                          ph.recon == MHD_RECON_PPH && !(XF && fc));
+        if (i >= z0 + 1) {
+          const int f = i - 1;
+          const double *bg = S.tab[f & 7] + TAB_FACE;
+          const FaceBg<R> bgf = {(R)bg[0], (R)bg[1], (R)bg[2], (R)bg[3]};
+          const Side<R> topk = {st[0], st[1], st[2], st[3], st[4],
+                                st[5], st[6], st[7], st[8]};
+          R fz[7];
+          face_flux<R, GR>(XF && (fk | fc) != 0, topk, botn, (R)bzf, bgf, (R)ph.gamma,
+                           (R)ph.igm1, ph.xi_mode, (R)ph.mach_cut, (R)ph.imach_cut, fz);
+          // mass flux for the species: the lower face of cell i-1 (and the
+          // top wall), written once, by the block that owns the cell
+          if (XF && p.mfz && t.owner && (f < z1 || (ph.reflect && f == ph.nz)))
+            plane_st(p.mfz + (size_t)f * plane, lane_off(t.col), (double)fz[0]);
+          to_cons<R>(2, fz, fzc);
+          S.zey[b][e] = -fz[5];  // z-face E_y = -F_z[B_x]
+          S.zex[b][e] = fz[6];   // z-face E_x = +F_z[B_y]
+          S.zm[b][e] = fz[0];
+        }
+      }
+      // cells of plane i-2: their flux divergence, and the values of the update
+      // that the next step finishes; then the next plane's cells.  All are in
+      // flight over the barrier.
+      const int kc = max(i - 2, 0);
+      const size_t pqc = (size_t)kc * plane;
+      const bool upd = i >= z0 + 2 && t.owner;
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        renew(us[f]);
+        u0[f] = 0.0;
+      }
+      if (upd) {
+        const uint32_t o = lane_off(t.col);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) us[f] = plane_ld(p.Us + f * ncell + pqc, o);
+      }
+      if (upd && ca != 0.0) {
+        const uint32_t o = lane_off(t.col);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) u0[f] = plane_ld(p.U0 + f * ncell + pqc, o);
+      }
+#pragma unroll
+      for (int f = 0; f < PRE_N; ++f) renew(pre[f]);
+      if (i <= z1) {
+        int mirn;
+        const int kn = zsource(ph, i + 1, mirn);
+        request_cell(ph, p, tile_off(ph, t), kn, pre);
+      }
+      {
+        const StageIdx ix = idx_rows(t.tid);
+        const int e = ix.e;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+          const R fxl = S.fx[pb][f][e], fyl = S.fy[pb][f][e];
+          const double acc = ((double)S.fx[pb][f][e + 1] - (double)fxl) * ph.idx +
+                             ((double)S.fy[pb][f][e + EP] - (double)fyl) * ph.idy;
+          r[f] = acc + ((double)fzc[f] - (double)st[9 + f]) * ph.idz;
+          // mass fluxes for the species: the lower x and y faces
+          if (XF && f == 0 && p.mfx && upd) {
+            plane_st(p.mfx + pqc, lane_off(t.col), (double)fxl);
+            plane_st(p.mfy + pqc, lane_off(t.col), (double)fyl);
+          }
+        }
+      }
+      if (!LATE && upd) finish(i - 2);
+      st[0] = topn.drho;
+      st[1] = topn.vn;
+      st[2] = topn.v1;
+      st[3] = topn.v2;
+      st[4] = topn.dp;
+      st[5] = topn.b1;
+      st[6] = topn.b2;
+      st[7] = GR ? topn.dge : R(0);
+      st[8] = GR ? topn.dgc : R(0);
+#pragma unroll
+      for (int f = 0; f < 5; ++f) st[9 + f] = fzc[f];
+      fk = fc;
+      fc = fn;
+    }
+    __syncthreads();
   }
-  if (bad) atomicOr(p.flags, bad);
+}
+
+// Face states of one face direction (AX 0: x, 1: y) at the lane's lower
+// face: reconstructs the own cell from the staged plane; the L state is the
+// upper value of the cell one down the axis, the previous lane of the row.
+template <typename R, bool GR, int AX>
+__device__ __forceinline__ void face_states(const R (*W)[LP], int w, bool pph, R *Wc,
+                                            Side<R> &L, Side<R> &Rt) {
+  constexpr int NF = Cfg<R, GR>::NF;
+  constexpr int ST = AX == 0 ? 1 : LW;
+  R m[NF], u[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    m[f] = W[f][w - ST];
+    Wc[f] = W[f][w];
+    u[f] = W[f][w + ST];
+  }
+  Side<R> hi;
+  recon_cell<R, GR>(AX, m, Wc, u, Rt, hi, pph);
+  L = side_from_left<R>(hi);
+}
+
+// background at the x- and y-faces of plane k
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ FaceBg<R> cell_bg(const StageLds<R, GR, XF> &S, int k) {
+  const double *bg = S.tab[k & 7];
+  return {(R)bg[0], (R)bg[1], (R)bg[2], (R)bg[3]};
+}
+
+// x-face waves, step i: the edges E_y on the z-face i-2 and the updates of
+// B_x and B_z (plane i-3) and B_y (plane i-4), then the x-faces of plane i-1.
+// st: 0 x-face E_y, 1 its mass flux, 2 the cell's reference E_y (plane
+// i-2), 3..5 the same of plane i-3, 6 edge E_y, 7 edge E_x (z-face i-3),
+// 8, 9 edge E_z of plane i-4, own and right.
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void xedge_step(const StageArgs &A, StageLds<R, GR, XF> &S,
+                                           const StageTile &t, double cdt, int i, R (&st)[XST_N],
+                                           const double (&pre)[XPRE_N]) {
+  const int z0 = t.z0, z1 = t.z1;
+  const Phys &ph = A.ph;
+  const StagePtrs &p = A.p;
+  const double ca = A.ca, cb = A.cb;
+  const size_t plane = (size_t)ph.nx * ph.ny;
+  const int b = i & 1, pb = b ^ 1;
+  const StageIdx ix = idx_rows(t.tid);
+  const int e = ix.e;
+  R ey_n = 0;
+  if (i >= z0 + 2 && i <= z1 + 2) {
+    // E_y at (ci-1/2, cj, i-2): a = z (z-faces at ci, ci-1), b = x
+    // (x-faces at planes i-2, i-3)
+    const R zey = S.zey[pb][e], zm = S.zm[pb][e];
+    const R zey_l = from_left(zey), zm_l = from_left(zm);
+    const R r_l = from_left(st[2]), rp_l = from_left(st[5]);
+    ey_n = ct_edge<R>(zey, zey_l, st[0], st[3], st[2], st[5], r_l, rp_l, zm, zm_l,
+                      st[1], st[4]);
+    // a reflecting wall carries no tangential EMF
+    if (ph.reflect && (i == 2 || i - 2 == ph.nz)) ey_n = R(0);
+  }
+  if (i >= z0 + 3) {
+    const R ex_n = S.ex[pb][e], ex_u = S.ex[pb][e + EP];
+    const R ez_c = S.ez[pb][e], ez_u = S.ez[pb][e + EP], ez_r = S.ez[pb][e + 1];
+    const R ey_p = st[6], ey_r = from_right(ey_p);
+    if (t.owner && i <= z1 + 2) {
+      const size_t px = (size_t)(i - 3) * plane;
+      const double rbx = ((double)ez_u - (double)ez_c) * ph.idy -
+                         ((double)ey_n - (double)ey_p) * ph.idz;
+      plane_st(p.Bxo + px, lane_off(t.col), cb * pre[0] - cdt * rbx + ca * pre[3]);
+    }
+    if (t.owner && i <= z1 + 2 && !(ph.reflect && i == 3)) {
+      const size_t px = (size_t)(i - 3) * plane;
+      const double rbz = ((double)ey_r - (double)ey_p) * ph.idx -
+                         ((double)ex_u - (double)ex_n) * ph.idy;
+      plane_st(p.Bzo + px, lane_off(t.col), cb * pre[2] - cdt * rbz + ca * pre[5]);
+    }
+    if (t.owner && i >= z0 + 4) {
+      const double rby = ((double)ex_n - (double)st[7]) * ph.idz -
+                         ((double)st[9] - (double)st[8]) * ph.idx;
+      plane_st(p.Byo + (size_t)(i - 4) * plane, lane_off(t.col),
+               cb * pre[1] - cdt * rby + ca * pre[4]);
+    }
+    st[7] = ex_n;
+    st[8] = ez_c;
+    st[9] = ez_r;
+  }
+  st[6] = ey_n;
+}
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void xface_step(const StageArgs &A, StageLds<R, GR, XF> &S,
+                                           const StageTile &t, int i, R (&st)[XST_N],
+                                           double (&pre)[XPRE_N]) {
+  constexpr int NF = Cfg<R, GR>::NF;
+  const Phys &ph = A.ph;
+  const StagePtrs &p = A.p;
+  const double ca = A.ca;
+  const int z0 = t.z0, z1 = t.z1;
+  const size_t plane = (size_t)ph.nx * ph.ny;
+  const int b = i & 1, pb = b ^ 1;
+  const StageIdx ix = idx_rows(t.tid);
+  const int e = ix.e;
+  if (i >= z0 && i <= z1 + 1) {
+    st[3] = st[0];
+    st[4] = st[1];
+    st[5] = st[2];
+    int fc = 0;
+    if (XF) fc = S.fl[XF ? pb : 0][XF ? e : 0];
+    R Wc[NF];
+    Side<R> L, Rt;
+    face_states<R, GR, 0>(S.w[pb], ix.w, ph.recon == MHD_RECON_PPH && !(XF && fc), Wc, L, Rt);
+    st[2] = -(Wc[Q_VZ] * Wc[Q_BX] - Wc[Q_VX] * Wc[Q_BZ]);
+    const bool hll = XF && (fc | dpp_shr1(fc)) != 0;  // cells ci-1 and ci
+    R fx[7], fxc[5];
+    face_flux<R, GR>(hll, L, Rt, S.bx[pb][e], cell_bg(S, i - 1), (R)ph.gamma,
+                     (R)ph.igm1, ph.xi_mode, (R)ph.mach_cut, (R)ph.imach_cut, fx);
+    to_cons<R>(0, fx, fxc);
+#pragma unroll
+    for (int f = 0; f < 5; ++f) S.fx[b][f][e] = fxc[f];
+    S.xez[b][e] = -fx[5];  // x-face E_z = -F_x[B_y]
+    st[0] = fx[6];       // x-face E_y = +F_x[B_z]
+    st[1] = fx[0];
+  }
+  // the face fields the next step updates
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    renew(pre[f]);
+    pre[3 + f] = 0.0;
+  }
+  const bool next = i >= z0 + 2 && t.owner;
+  const size_t nx = (size_t)max(0, min(i - 2, z1 - 1)) * plane;
+  const size_t ny = (size_t)max(0, min(max(i - 3, z0), z1 - 1)) * plane;
+  if (next) {
+    const uint32_t o = lane_off(t.col);
+    pre[0] = plane_ld(p.Bxs + nx, o);
+    pre[1] = plane_ld(p.Bys + ny, o);
+    pre[2] = plane_ld(p.Bzs + nx, o);
+  }
+  if (next && ca != 0.0) {
+    const uint32_t o = lane_off(t.col);
+    pre[3] = plane_ld(p.Bx0 + nx, o);
+    pre[4] = plane_ld(p.By0 + ny, o);
+    pre[5] = plane_ld(p.Bz0 + nx, o);
+  }
+}
+
+// y-face waves (lanes of a row run along y), step i: the edges E_x on the
+// z-face i-2 and E_z of plane i-2, then the y-faces of plane i-1.
+// st: 0 y-face E_x, 1 its E_z, 2 its mass flux, 3, 4 the cell's reference
+// E_x, E_z (plane i-2), 5..7 E_x, mass flux, reference E_x of plane i-3.
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void yedge_step(const StageArgs &A, StageLds<R, GR, XF> &S,
+                                           const StageTile &t, int i, R (&st)[YST_N]) {
+  const int z0 = t.z0, z1 = t.z1;
+  const Phys &ph = A.ph;
+  const int b = i & 1, pb = b ^ 1;
+  const StageIdx ix = idx_cols(t.tid);
+  const int e = ix.e;
+  if (i >= z0 + 2 && i <= z1 + 2) {
+    // E_x at (ci, cj-1/2, i-2): a = y (y-faces at planes i-2, i-3), b = z
+    // (z-faces at cj, cj-1)
+    const R zex = S.zex[pb][e], zm = S.zm[pb][e];
+    const R zex_d = from_left(zex), zm_d = from_left(zm);
+    const R rx_d = from_left(st[3]), rxp_d = from_left(st[7]);
+    R ex_n = ct_edge<R>(st[0], st[5], zex, zex_d, st[3], rx_d, st[7], rxp_d, st[2],
+                        st[6], zm, zm_d);
+    if (ph.reflect && (i == 2 || i - 2 == ph.nz)) ex_n = R(0);
+    S.ex[b][e] = ex_n;
+    // E_z at (ci-1/2, cj-1/2, i-2): a = x, b = y
+    const R xez = S.xez[pb][e], xm = S.fx[pb][0][e];
+    const R xez_d = from_left(xez), xm_d = from_left(xm);
+    const R yez_l = S.yez[pb][e - 1], ym_l = S.fy[pb][0][e - 1], rz_l = S.rz[pb][e - 1];
+    const R rz_d = from_left(st[4]), rz_ld = from_left(rz_l);
+    S.ez[b][e] = ct_edge<R>(xez, xez_d, st[1], yez_l, st[4], rz_l, rz_d, rz_ld, xm, xm_d,
+                            st[2], ym_l);
+  }
+}
+template <typename R, bool GR, bool XF>
+__device__ __forceinline__ void yface_step(const StageArgs &A, StageLds<R, GR, XF> &S,
+                                           const StageTile &t, int i, R (&st)[YST_N]) {
+  constexpr int NF = Cfg<R, GR>::NF;
+  const Phys &ph = A.ph;
+  const int z0 = t.z0, z1 = t.z1;
+  const int b = i & 1, pb = b ^ 1;
+  const StageIdx ix = idx_cols(t.tid);
+  const int e = ix.e;
+  if (i >= z0 && i <= z1 + 1) {
+    st[5] = st[0];
+    st[6] = st[2];
+    st[7] = st[3];
+    int fc = 0;
+    if (XF) fc = S.fl[XF ? pb : 0][XF ? e : 0];
+    R Wc[NF];
+    Side<R> L, Rt;
+    face_states<R, GR, 1>(S.w[pb], ix.w, ph.recon == MHD_RECON_PPH && !(XF && fc), Wc, L, Rt);
+    st[3] = -(Wc[Q_VY] * Wc[Q_BZ] - Wc[Q_VZ] * Wc[Q_BY]);
+    st[4] = -(Wc[Q_VX] * Wc[Q_BY] - Wc[Q_VY] * Wc[Q_BX]);
+    S.rz[b][e] = st[4];
+    const bool hll = XF && (fc | dpp_shr1(fc)) != 0;  // cells cj-1 and cj
+    R fy[7], fyc[5];
+    face_flux<R, GR>(hll, L, Rt, S.by[pb][e], cell_bg(S, i - 1), (R)ph.gamma,
+                     (R)ph.igm1, ph.xi_mode, (R)ph.mach_cut, (R)ph.imach_cut, fy);
+    to_cons<R>(1, fy, fyc);
+#pragma unroll
+    for (int f = 0; f < 5; ++f) S.fy[b][f][e] = fyc[f];
+    S.yez[b][e] = fy[6];  // y-face E_z = +F_y[B_x]
+    st[0] = -fy[5];     // y-face E_x = -F_y[B_z]
+    st[1] = fy[6];
+    st[2] = fy[0];
+  }
+}
+
+// March of the face waves.  FP64: x-faces and y-faces in waves of their own
+// (DO_X or DO_Y); FP32: both in one wave.
+template <typename R, bool GR, bool XF, bool DO_X, bool DO_Y>
+__device__ __forceinline__ void face_steps(const StageArgs &args, StageLds<R, GR, XF> &S,
+                                           const StageTile &t, const RingCell &rc, double cdt, int wv, int lane,
+                                           int &bad) {
+  // The ring cells go first with the gas + radiation EOS, whose inversion has
+  // the longest way to go (the registers of its 12 values are then free for
+  // the edges: 5.17 -> 4.92 ms for three steps of a 170 x 190 x 150 box in
+  // FP64), else after the edges, which hide the values' latency
+  constexpr bool RING = DO_Y, FIRST = GR;
+  const int z0 = t.z0, z1 = t.z1;
+  R xst[XST_N], yst[YST_N];
+#pragma unroll
+  for (int f = 0; f < XST_N; ++f) xst[f] = R(0);
+#pragma unroll
+  for (int f = 0; f < YST_N; ++f) yst[f] = R(0);
+  double pre[XPRE_N] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, rpre[PRE_N];
+  if (RING) ring_request(args.ph, args.p, rc, z0 - 2, rpre);
+  // the table row of the next plane is stored during a step, requested at
+  // the end of the step before
+  double tab = 0.0;
+  if (DO_X && wv == 0) tab = table_request(args.ph, args.p, z0 - 1, lane);
+  for (int i = z0 - 2; i <= z1 + 3; ++i) {
+    const StageArgs &A = stage_args_view();
+    if (FIRST && RING && i <= z1 + 1) ring_step<R, GR, XF>(A, S, rc, i, rpre, bad);
+    if (DO_X) xedge_step<R, GR, XF>(A, S, t, cdt, i, xst, pre);
+    if (DO_Y) yedge_step<R, GR, XF>(A, S, t, i, yst);
+    if (DO_X && wv == 0 && lane < TAB_N) S.tab[(i + 1) & 7][lane] = tab;
+    if (!FIRST && RING && i <= z1 + 1) ring_step<R, GR, XF>(A, S, rc, i, rpre, bad);
+    if (DO_X) xface_step<R, GR, XF>(A, S, t, i, xst, pre);
+    if (DO_Y) yface_step<R, GR, XF>(A, S, t, i, yst);
+    if (RING && i <= z1) ring_request(A.ph, A.p, rc, i + 1, rpre);
+    renew(tab);
+    if (DO_X && wv == 0) tab = table_request(A.ph, A.p, min(i + 2, z1 + 1), lane);
+    __syncthreads();
+  }
+}
+
+// XF: the optional features of a stage (forcing modes, shock-flattening
+// flags, species mass fluxes); the variant without them carries none of
+// their code, pointers or registers.
+template <typename R, bool GR, bool XF>
+__global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void stage_kernel(
+    StageArgs args) {
+  const Phys &ph = args.ph;
+  const StagePtrs &p = args.p;
+  static_assert(sizeof(MlpLds) % 16 == 0, "MlpLds is copied in 16-byte words");
+  __shared__ StageLds<R, GR, XF> S;
+
+  // the first four waves are the columns', the others the faces'; the role
+  // is the same for every lane of a wave
+  const int role = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS);
+  const int tid = threadIdx.x % NTHREADS;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave of the role
+  const int lx = tid % TT, ly = tid / TT;
+  const double cdt = uniform(args.cc * (p.dt_dev ? *p.dt_dev : args.dt_host));
+  StageCount n;
+  // The launch's items of work: the planes of one tile, first whole columns
+  // of planes (args.full for every block), then the columns of the remaining
+  // tiles cut in segments of args.share planes.  Tiles run fastest, so the
+  // blocks march up neighbouring tiles at the same heights, and the logical
+  // order gives each XCD a contiguous run of them: they share its L2.
+  const int nblk = gridDim.x, lb = xcd_logical_block(blockIdx.x, nblk);
+  for (int it = 0;; ++it) {
+    const StageArgs &A = stage_args_view();
+    const Phys &ph = A.ph;
+    int tile, z0, z1;
+    if (it < A.full) {
+      tile = it * nblk + lb;
+      z0 = 0;
+      z1 = ph.nz;
+    } else {
+      const int rest = A.tiles - A.full * nblk;
+      const int j = (it - A.full) * nblk + lb;
+      const int seg = rest > 0 ? j / rest : 0;
+      z0 = seg * A.share;
+      if (rest <= 0 || z0 >= ph.nz) break;
+      z1 = min(ph.nz, z0 + A.share);
+      tile = A.full * nblk + (j - seg * rest);
+    }
+    const int ntx = (ph.nx + TB - 1) / TB;
+    tile = __builtin_amdgcn_readfirstlane(tile);
+    z0 = __builtin_amdgcn_readfirstlane(z0);
+    z1 = __builtin_amdgcn_readfirstlane(z1);
+    const int X0 = (tile % ntx) * TB, Y0 = (tile / ntx) * TB;
+    const int gx = X0 + lx - 1, gy = Y0 + ly - 1;
+    const int gi = wrapi(gx, ph.nx), gj = wrapi(gy, ph.ny);
+    const RingCell rc = ring_cell(ph, X0, Y0, tid);
+    StageTile t;
+    t.z0 = z0;
+    t.z1 = z1;
+    t.tid = tid;
+    t.owner = lx >= 1 && lx <= TB && ly >= 1 && ly <= TB && gx < ph.nx && gy < ph.ny;
+    t.xedge = gi + 1 == ph.nx;
+    t.yedge = gj + 1 == ph.ny;
+    t.col = (uint32_t)(((size_t)gj * ph.nx + gi) * 8);
+    // the first plane's table row; the face waves bring one a step
+    if (role == 1 && wv == 0) {
+      const double v = table_request(ph, A.p, z0 - 2, tid & 63);
+      if ((tid & 63) < TAB_N) S.tab[(z0 - 2) & 7][tid & 63] = v;
+    }
+    __syncthreads();
+    if (role == 0)
+      column_steps<R, GR, XF>(A, S, t, cdt, n);
+    else if constexpr (sizeof(R) == 4)
+      face_steps<R, GR, XF, true, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+    else if (role == 1)
+      face_steps<R, GR, XF, true, false>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+    else
+      face_steps<R, GR, XF, false, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+  }
+  if (n.bad) atomicOr(p.flags, n.bad);
   if (GR) {
-    // block totals of the Newton statistics
-    __shared__ unsigned long long s_it[NTHREADS / 64], s_fb[NTHREADS / 64], s_mx[NTHREADS / 64];
-    unsigned long long a = nit, f = nfb, m = nmax;
+    // Newton statistics: wave totals of the column waves, then the block's
+    unsigned long long a = n.it, m = n.mx, f = n.fb;
     for (int o = 32; o > 0; o >>= 1) {
       a += __shfl_xor(a, o);
       f += __shfl_xor(f, o);
-      unsigned long long mo = __shfl_xor(m, o);
+      const unsigned long long mo = __shfl_xor(m, o);
       m = mo > m ? mo : m;
     }
-    if ((tid & 63) == 0) {
-      s_it[tid >> 6] = a;
-      s_fb[tid >> 6] = f;
-      s_mx[tid >> 6] = m;
+    if (role == 0 && (tid & 63) == 0) {
+      S.nst[0][tid >> 6] = a;
+      S.nst[GR ? 1 : 0][tid >> 6] = m;
+      S.nst[GR ? 2 : 0][tid >> 6] = f;
     }
     __syncthreads();
-    if (tid == 0) {
-      unsigned long long A = 0, Fb = 0, M = 0;
-      for (int w = 0; w < NTHREADS / 64; ++w) {
-        A += s_it[w];
-        Fb += s_fb[w];
-        M = s_mx[w] > M ? s_mx[w] : M;
+    if (threadIdx.x == 0) {
+      unsigned long long a = 0, m = 0, f = 0;
+      for (int v = 0; v < NTHREADS / 64; ++v) {
+        a += S.nst[0][v];
+        m = S.nst[GR ? 1 : 0][v] > m ? S.nst[GR ? 1 : 0][v] : m;
+        f += S.nst[GR ? 2 : 0][v];
       }
-      atomicAdd(&p.newton_stats[0], A);
-      atomicMax(&p.newton_stats[1], M);
-      atomicAdd(&p.newton_stats[2], Fb);
+      atomicAdd(&p.newton_stats[0], a);
+      atomicMax(&p.newton_stats[1], m);
+      atomicAdd(&p.newton_stats[2], f);
     }
   }
 }
@@ -806,13 +1028,13 @@ size_t mlp_bytes() { return sizeof(MlpLds); }
 template <typename R, bool GR>
 static void launch_stage_g(const Ctx &c, const StagePtrs &p, double a, double b, double cc,
                            double dt_host, dim3 grid) {
-  dim3 block(NTHREADS);
+  dim3 block(stage_threads<R>());
   if (p.fcoef || p.flat || p.mfx || p.mfy || p.mfz)
     hipLaunchKernelGGL((stage_kernel<R, GR, true>), grid, block, 0, c.stream,
-                       StageArgs{c.ph, p, a, b, cc, dt_host, c.zseg});
+                       StageArgs{c.ph, p, a, b, cc, dt_host, c.stage_tiles, c.stage_full, c.stage_share});
   else
     hipLaunchKernelGGL((stage_kernel<R, GR, false>), grid, block, 0, c.stream,
-                       StageArgs{c.ph, p, a, b, cc, dt_host, c.zseg});
+                       StageArgs{c.ph, p, a, b, cc, dt_host, c.stage_tiles, c.stage_full, c.stage_share});
 }
 
 template <typename R>
@@ -837,18 +1059,18 @@ static const void *stage_fn(const Ctx &c) {
 }
 
 int stage_blocks_per_cu(const Ctx &c) {
-  const void *f = c.d.precision == MHD_PREC_SPLIT ? stage_fn<float>(c) : stage_fn<double>(c);
+  const bool split = c.d.precision == MHD_PREC_SPLIT;
+  const void *f = split ? stage_fn<float>(c) : stage_fn<double>(c);
+  const int nt = split ? stage_threads<float>() : stage_threads<double>();
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, NTHREADS, 0) != hipSuccess || nb < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, nt, 0) != hipSuccess || nb < 1)
     nb = 1;
   return nb;
 }
 
 hipError_t launch_stage(const Ctx &c, const StagePtrs &p, double a, double b,
                         double cc, double dt_host) {
-  const Phys &ph = c.ph;
-  const int nblk = ((ph.nx + TB - 1) / TB) * ((ph.ny + TB - 1) / TB) * ((ph.nz + c.zseg - 1) / c.zseg);
-  dim3 grid(nblk);
+  dim3 grid(c.stage_blocks);
   if (c.d.precision == MHD_PREC_SPLIT)
     launch_stage_t<float>(c, p, a, b, cc, dt_host, grid);
   else

@@ -172,12 +172,8 @@ int latched(mhd_ctx *h) {
 // steps is taken.  MHD_ZSEG (planes per segment, no whole columns) overrides
 // the choice for tuning and tests.
 constexpr long long STAGE_STEPS = 5;
-void split_stage_work(mhd::Ctx &c, int dev) {
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus < 1)
-    cus = 256;
-  const long long slots = (long long)cus * mhd::stage_blocks_per_cu(c), nz = c.ph.nz;
+void split_stage_work(mhd::Ctx &c) {
+  const long long slots = (long long)c.cus * mhd::stage_blocks_per_cu(c), nz = c.ph.nz;
   const long long tiles = (long long)((c.ph.nx + mhd::TB - 1) / mhd::TB) *
                           ((c.ph.ny + mhd::TB - 1) / mhd::TB);
   long long best = -1, items = 1;
@@ -300,7 +296,12 @@ int mhd_init_grid(const mhd_grid_desc *desc, void *hip_stream, mhd_ctx **out) {
   mhd::fill_phys(desc, ph);
   c.ncell = (size_t)desc->nx * desc->ny * desc->nz;
   c.nfz = (size_t)desc->nx * desc->ny * ph.nzf;
-  split_stage_work(c, dev);
+  if (hipDeviceGetAttribute(&c.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      c.cus < 1)
+    c.cus = 256;
+  split_stage_work(c);
+  if (desc->nspecies > 0) c.species_zseg = mhd::species_segment(c);
+  if (desc->flatten) c.flag_zseg = mhd::shock_flag_segment(c);
 
   auto cleanup = [&](hipError_t e, const char *what) {
     g_init_err = std::string(what) + ": " + hipGetErrorString(e);

@@ -73,10 +73,14 @@ __global__ __launch_bounds__(256) void diff_init_kernel(
 // A block owns a 64 x 4 column tile and a z segment and marches up it: the
 // column's T and chi of planes k-1, k, k+1 stay in registers (the z
 // neighbours), the tile's plane k with a one-cell ring is staged in LDS
-// (the x and y neighbours), so T and chi are read from HBM about once.
+// (the x and y neighbours), so T and chi are read from HBM about once.  The
+// kernel moves 80 B a cell (72 in the temperature form) and waits on them
+// most of the time (four waves per SIMD, vector pipe 47 % busy): the other
+// values of a plane are requested before its staging and barrier, and short
+// segments keep more blocks in flight (192^3: 159 us a stage with 16 planes
+// and the values loaded at their use, 140 us now).
 constexpr int DTX = 64, DTY = 4;                // tile (256 threads)
 constexpr int DLX = DTX + 2, DLY = DTY + 2;     // staged plane with its ring
-constexpr int DZSEG = 16;                       // planes per block
 
 template <bool TF>
 __global__ __launch_bounds__(256) void diff_stage_kernel(
@@ -85,18 +89,17 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
     const double *__restrict__ y1, const double *__restrict__ y2, double *__restrict__ M0,
     const double *__restrict__ cv0, int first, double mu, double nu, double mut,
     double gamt, double dt, double *__restrict__ yn, double *__restrict__ Tb,
-    double *__restrict__ chib, int *flags) {
+    double *__restrict__ chib, int *flags, int zseg) {
   __shared__ double sT[DLY][DLX], sC[DLY][DLX];
   const size_t plane = (size_t)ph.nx * ph.ny;
   const double *rho = U;
-  const double *yp = TF ? Ta : y1;
   const int tid = threadIdx.x;
   const int tx = tid % DTX, ty = tid / DTX;
   const int ntx = (ph.nx + DTX - 1) / DTX, nty = (ph.ny + DTY - 1) / DTY;
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int btx = lb % ntx, bty = (lb / ntx) % nty, bz = lb / (ntx * nty);
   const int X0 = btx * DTX, Y0 = bty * DTY;
-  const int z0 = bz * DZSEG, z1 = min(z0 + DZSEG, ph.nz);
+  const int z0 = bz * zseg, z1 = min(z0 + zseg, ph.nz);
   const int gx = X0 + tx, gy = Y0 + ty;
   const bool own = gx < ph.nx && gy < ph.ny;
   const size_t col = (size_t)wrapi(gy, ph.ny) * ph.nx + wrapi(gx, ph.nx);
@@ -109,6 +112,20 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
     // the next plane's values are requested before this plane is evaluated
     const double tn = Ta[zp(k + 1)], cn = chia[zp(k + 1)];
     const size_t pk = (size_t)k * plane;
+    const size_t q = pk + col;
+    // the cell's own values of the combination, in flight over the staging of
+    // the plane and its barrier
+    double r = 0.0, v0 = 0.0, v1 = 0.0, v2 = 0.0, m0 = 0.0, cv = 0.0;
+    if (own) {
+      r = rho[q];
+      v0 = y0[q];
+      if (TF) cv = cv0[q];
+      if (!first) {
+        v1 = TF ? tc : y1[q];
+        v2 = y2[q];
+        m0 = M0[q];
+      }
+    }
     sT[ty + 1][tx + 1] = tc;
     sC[ty + 1][tx + 1] = ccur;
     for (int h = tid; h < DLX * DLY - DTX * DTY; h += 256) {
@@ -130,7 +147,6 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
       sC[hy][hx] = chia[qh];
     }
     __syncthreads();
-    const size_t q = pk + col;
     // M[T]: the face fluxes in the order x-, x+, y-, y+, z-, z+
     double div = 0.0;
     auto face = [&](double tnb, double cnb, double inv_dx) {
@@ -148,16 +164,14 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
       if (!(ph.reflect && k + 1 == ph.nz)) div += face(tn, cn, ph.idz);
     }
     if (own) {
-      const double r = rho[q];
       double M = div * rcp<double>(r);
-      if (TF) M *= rcp<double>(cv0[q]);
+      if (TF) M *= rcp<double>(cv);
       double v;
       if (first) {
         M0[q] = M;
-        v = y0[q] + mut * dt * M;
+        v = v0 + mut * dt * M;
       } else {
-        v = mu * yp[q] + nu * y2[q] + (1.0 - mu - nu) * y0[q] + mut * dt * M +
-            gamt * dt * M0[q];
+        v = mu * v1 + nu * v2 + (1.0 - mu - nu) * v0 + mut * dt * M + gamt * dt * m0;
       }
       yn[q] = v;
       double t = v;
@@ -275,21 +289,30 @@ hipError_t launch_diff_init(const Ctx &c, const double *U, const double *Bx, con
   return hipGetLastError();
 }
 
+// Planes per block: eight where that makes 16 blocks per CU (four rounds of
+// the four resident ones), else four.  A super step of 20 stages: 256^3 8.01
+// ms with eight, 8.15 with four (8.22 with sixteen); 192^3 3.54 and 3.50;
+// 96 x 90 x 101 0.83 and 0.72 (1.23 with sixteen).
+static int diff_segment(long long tiles, const Ctx &c) {
+  return tiles * ((c.ph.nz + 7) / 8) >= 16ll * c.cus ? 8 : 4;
+}
+
 hipError_t launch_diff_stage(const Ctx &c, const double *U, const double *Ta, const double *chia,
                              const double *y0, const double *y1, const double *y2, double *yn,
                              double *Tb, double *chib, int tform, int first, double mu,
                              double nu, double mut, double gamt, double dt) {
   const DiffBufs &d = c.diff;
-  const dim3 grid(((c.ph.nx + DTX - 1) / DTX) * ((c.ph.ny + DTY - 1) / DTY) *
-                  ((c.ph.nz + DZSEG - 1) / DZSEG));
+  const int tiles = ((c.ph.nx + DTX - 1) / DTX) * ((c.ph.ny + DTY - 1) / DTY);
+  const int zseg = diff_segment(tiles, c);
+  const dim3 grid(tiles * ((c.ph.nz + zseg - 1) / zseg));
   if (tform)
     hipLaunchKernelGGL(diff_stage_kernel<true>, grid, dim3(256), 0, c.stream,
                        c.ph, c.dparams, U, Ta, chia, y0, y1, y2, d.M0, d.cv0, first, mu, nu,
-                       mut, gamt, dt, yn, Tb, chib, c.flags);
+                       mut, gamt, dt, yn, Tb, chib, c.flags, zseg);
   else
     hipLaunchKernelGGL(diff_stage_kernel<false>, grid, dim3(256), 0, c.stream,
                        c.ph, c.dparams, U, Ta, chia, y0, y1, y2, d.M0, d.cv0, first, mu, nu,
-                       mut, gamt, dt, yn, Tb, chib, c.flags);
+                       mut, gamt, dt, yn, Tb, chib, c.flags, zseg);
   return hipGetLastError();
 }
 

@@ -59,9 +59,8 @@ __global__ __launch_bounds__(256) void shock_pressure_kernel(
 constexpr int FX = 16, FY = 16;           // output tile (256 threads)
 constexpr int PX = FX + 6, PY = FY + 6;   // pressure tile (halo 3)
 constexpr int DX = FX + 4, DY = FY + 4;   // detector tile (halo 2)
-constexpr int FZSEG = 32;                 // planes per block
 
-__global__ __launch_bounds__(256) void shock_flag_kernel(Phys ph, double eps,
+__global__ __launch_bounds__(256) void shock_flag_kernel(Phys ph, double eps, int zseg,
                                                          const double *__restrict__ P,
                                                          uint8_t *__restrict__ out) {
   __shared__ double sP[3][PY][PX];
@@ -73,7 +72,7 @@ __global__ __launch_bounds__(256) void shock_flag_kernel(Phys ph, double eps,
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int btx = lb % ntx, bty = (lb / ntx) % nty, bz = lb / (ntx * nty);
   const int X0 = btx * FX, Y0 = bty * FY;
-  const int z0 = bz * FZSEG, z1 = min(z0 + FZSEG, ph.nz);
+  const int z0 = bz * zseg, z1 = min(z0 + zseg, ph.nz);
   const size_t plane = (size_t)ph.nx * ph.ny;
   const int gx = X0 + tx, gy = Y0 + ty;
   const bool own = gx < ph.nx && gy < ph.ny;
@@ -182,11 +181,23 @@ hipError_t launch_shock_pressure(const Ctx &c, const double *U, const double *Bx
   return hipGetLastError();
 }
 
+// Planes per block of the flag kernel.  A segment costs four extra planes;
+// four blocks per CU hide its latencies (three barriers a plane), and beyond
+// 32 planes a longer segment gains nothing (256^3: 0.121 ms a launch with 32,
+// 0.133 to 0.135 with 48 and 64; 160 x 144 x 128, which 32 planes leave at 1.4
+// blocks per CU: 48 us, with the 12 taken here 35).
+constexpr int FSLOTS = 4, FEXTRA = 4, FZMAX = 32;
+int shock_flag_segment(const Ctx &c) {
+  const long long tiles = (long long)((c.ph.nx + FX - 1) / FX) * ((c.ph.ny + FY - 1) / FY);
+  const int len = segment_planes(tiles, c.ph.nz, (long long)c.cus * FSLOTS, FEXTRA);
+  return len < FZMAX ? len : FZMAX;
+}
+
 hipError_t launch_shock_flags(const Ctx &c) {
   const int nb = ((c.ph.nx + FX - 1) / FX) * ((c.ph.ny + FY - 1) / FY) *
-                 ((c.ph.nz + FZSEG - 1) / FZSEG);
+                 ((c.ph.nz + c.flag_zseg - 1) / c.flag_zseg);
   hipLaunchKernelGGL(shock_flag_kernel, dim3(nb), dim3(256), 0, c.stream, c.ph, c.d.eps_sf,
-                     c.shock_p, c.shock_f);
+                     c.flag_zseg, c.shock_p, c.shock_f);
   return hipGetLastError();
 }
 

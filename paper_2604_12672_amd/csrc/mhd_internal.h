@@ -87,6 +87,26 @@ struct DiffBufs {
   double *cv0 = nullptr;                // c_v at the start
 };
 
+// Planes per segment for blocks that march up columns of nz planes: `tiles`
+// columns cut in equal segments, worked off in rounds of `slots` resident
+// blocks, a segment of n planes costing n + extra steps (the extra ones fill
+// the march).  Returns the length that costs the fewest steps.
+inline int segment_planes(long long tiles, int nz, long long slots, int extra) {
+  long long best = -1;
+  int len = nz;
+  for (int segs = 1; segs <= nz; ++segs) {
+    const int l = (nz + segs - 1) / segs;
+    const long long n = tiles * ((nz + l - 1) / l);
+    const long long cost = (n + slots - 1) / slots * (l + extra);
+    if (best < 0 || cost < best) {
+      best = cost;
+      len = l;
+    }
+    if (segs >= 256) break;
+  }
+  return len;
+}
+
 struct Ctx {
   mhd_grid_desc d;
   Phys ph;
@@ -134,6 +154,9 @@ struct Ctx {
   // stage_full whole columns of planes, the columns of the remaining tiles
   // are cut in segments of stage_share planes; zseg is the longest segment
   int stage_tiles = 1, stage_blocks = 1, stage_full = 0, stage_share = 1, zseg = 1;
+  int cus = 256;  // compute units of the device
+  // planes per segment of the species and flag kernels
+  int species_zseg = 1, flag_zseg = 1;
   std::string err;
 };
 
@@ -198,6 +221,9 @@ hipError_t launch_shock_pressure(const Ctx &c, const double *U, const double *Bx
                                  const double *By, const double *Bz, const double *Tg,
                                  int newton_cap);
 hipError_t launch_shock_flags(const Ctx &c);
+int shock_flag_segment(const Ctx &c);
+// planes per segment of the species kernel of the context
+int species_segment(const Ctx &c);
 // species update of one RK stage (mhd_species.hip): Xo = a X0 + b Xs -
 // c dt div(F_mass X_up); rho is the stage input density
 hipError_t launch_species(const Ctx &c, const double *rho, const double *Xs, const double *X0,

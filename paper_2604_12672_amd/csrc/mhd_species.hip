@@ -98,7 +98,6 @@ __device__ __forceinline__ double pair_other(double v) {
 constexpr int SP_TX = 16, SP_TY = 8;                          // columns per tile
 constexpr int SP_HX = SP_TX + 4, SP_HY = SP_TY + 4;           // staged plane
 constexpr int SP_HALO = SP_HX * SP_HY - SP_TX * SP_TY;        // 112 halo cells
-constexpr int SP_ZSEG = 32;                                   // planes per block
 
 // LDS position of halo cell h (0 <= h < SP_HALO): the two rows below and
 // above the tile (full width), then the two columns either side
@@ -332,6 +331,30 @@ __global__ __launch_bounds__(256) void species_kernel(Phys ph, SpeciesPtrs p, in
   }
 }
 
+// the kernel variant for the species count (register arrays sized for it)
+static const void *species_fn(int ns) {
+  return ns <= 4    ? reinterpret_cast<const void *>(&species_kernel<2>)
+         : ns <= 8  ? reinterpret_cast<const void *>(&species_kernel<4>)
+         : ns <= 12 ? reinterpret_cast<const void *>(&species_kernel<6>)
+                    : reinterpret_cast<const void *>(&species_kernel<8>);
+}
+
+// Planes per block: equal segments in as few rounds of the resident blocks
+// as the march's three extra planes allow.  12 species at 112^3 (98 tiles,
+// two blocks per CU): 321 us a launch with 32 planes (392 blocks, the last
+// segment half empty), 256 with 28; 190 x 180 x 200 6.89 -> 6.59 ms a step,
+// five species at 64 x 60 x 70 1.35 -> 0.69 ms for two steps.
+int species_segment(const Ctx &c) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, species_fn(c.d.nspecies), 256, 0) !=
+          hipSuccess ||
+      nb < 1)
+    nb = 1;
+  const long long tiles =
+      (long long)((c.ph.nx + SP_TX - 1) / SP_TX) * ((c.ph.ny + SP_TY - 1) / SP_TY);
+  return segment_planes(tiles, c.ph.nz, (long long)c.cus * nb, 3);
+}
+
 hipError_t launch_species(const Ctx &c, const double *rho, const double *Xs, const double *X0,
                           double *Xo, double a, double b, double cc, double dt_host,
                           const double *dt_dev, const uint8_t *flat) {
@@ -346,7 +369,7 @@ hipError_t launch_species(const Ctx &c, const double *rho, const double *Xs, con
   p.flat = flat;
   p.dt_dev = dt_dev;
   const int ns = c.d.nspecies;
-  const int zseg = SP_ZSEG;
+  const int zseg = c.species_zseg;
   // per-lane offsets within a plane are 32-bit byte offsets
   if ((unsigned long long)c.ph.nx * c.ph.ny * sizeof(double) >= (1ull << 32))
     return hipErrorInvalidValue;

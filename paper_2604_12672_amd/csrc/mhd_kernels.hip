@@ -429,8 +429,17 @@ __device__ __forceinline__ RingCell ring_cell(const Phys &ph, int X0, int Y0, in
                   wrapi(Y0 + cj + 1, ph.ny))};
 }
 
+// FLAT: a grid of one plane.  Every plane of the march is the same one, so
+// its cells are converted once (step z0-1, into both slots), its faces solved
+// once (step z0+1), and steps z0-2 and z0 are left out.  Where a step needs
+// values of the plane below or above, its own are those.
+template <bool FLAT>
+__device__ __forceinline__ bool skip_step(int i, int z0) {
+  return FLAT && (i == z0 - 2 || i == z0);
+}
+
 // the requested ring cell of plane i to the staged plane
-template <typename R, bool GR, bool XF>
+template <typename R, bool GR, bool XF, bool FLAT>
 __device__ __forceinline__ void ring_step(const StageArgs &A, StageLds<R, GR, XF> &S,
                                           const RingCell &rc, int i, const double *pre, int &bad) {
   constexpr int NF = Cfg<R, GR>::NF;
@@ -443,7 +452,10 @@ __device__ __forceinline__ void ring_step(const StageArgs &A, StageLds<R, GR, XF
     prim_cell<R, GR>(A.ph, pre, bg, mir, Wr, o, A.p.newton_cap);
     bad |= o.bad;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) S.w[i & 1][f][rc.w] = Wr[f];
+    for (int f = 0; f < NF; ++f) {
+      S.w[i & 1][f][rc.w] = Wr[f];
+      if (FLAT) S.w[~i & 1][f][rc.w] = Wr[f];
+    }
   }
 }
 // ... and the request of plane i
@@ -471,7 +483,7 @@ struct StageCount {
 // Column waves, step i: primitives of plane i, the z-face between cells i-2
 // and i-1, the update of the cells of plane i-2.
 // st: 0..8 upper z-face state of cell i-2, 9..13 z-face flux of the face i-2.
-template <typename R, bool GR, bool XF>
+template <typename R, bool GR, bool XF, bool FLAT>
 __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, GR, XF> &S,
                                              const StageTile &t, double cdt, StageCount &n) {
   constexpr int NF = Cfg<R, GR>::NF;
@@ -504,6 +516,7 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
       fco[XF ? d : 0] = plane_ld((const R *)args.p.fcoef + d * plane, lane_off(t.col / (8 / sizeof(R))));
   }
   for (int i = z0 - 2; i <= z1 + 3; ++i) {
+    if (skip_step<FLAT>(i, z0)) continue;
     const StageArgs &A = stage_args_view();
     const Phys &ph = A.ph;
     const StagePtrs &p = A.p;
@@ -557,14 +570,14 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
         bzf = plane_ld(p.Bzs + (size_t)zface(ph, i - 1) * plane, lane_off(t.col));
       // primitives of plane i, staged for the face waves
       R Wn[NF];
-      {
+      if (!FLAT || i < z0) {
         const double *bg = S.tab[i & 7];
         PrimOut o;
         prim_cell<R, GR>(ph, pre, bg, mir, Wn, o, p.newton_cap);
         S.bx[b][e] = (R)pre[5];
         S.by[b][e] = (R)pre[6];
         if (GR) {
-          if (t.owner && i >= z0 && i < z1) {
+          if (t.owner && (FLAT ? i < z0 : i >= z0 && i < z1)) {
             if (p.Tout) plane_st(p.Tout + (size_t)kk * plane, lane_off(t.col), o.T);
             n.it += o.iters;
             n.mx = (unsigned)o.iters > n.mx ? o.iters : n.mx;
@@ -573,22 +586,37 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
         }
         n.bad |= o.bad;
       }
-      if (XF) S.fl[b][e] = (uint8_t)fn;
+      if (XF && (!FLAT || i < z0)) S.fl[b][e] = (uint8_t)fn;
       // own cells i-2 (its slot is the one plane i goes to; only this thread
       // reads or writes that slot) and i-1
       R Wm[NF], Wc[NF];
+      if (!FLAT) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        Wm[f] = S.w[b][f][w];
-        Wc[f] = S.w[pb][f][w];
-        S.w[b][f][w] = Wn[f];
+        for (int f = 0; f < NF; ++f) {
+          Wm[f] = S.w[b][f][w];
+          Wc[f] = S.w[pb][f][w];
+          S.w[b][f][w] = Wn[f];
+        }
+      } else if (i < z0) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) S.w[b][f][w] = S.w[pb][f][w] = Wn[f];
+        S.bx[pb][e] = S.bx[b][e];
+        S.by[pb][e] = S.by[b][e];
+        if (XF) S.fl[XF ? pb : 0][XF ? e : 0] = (uint8_t)fn;
+      } else {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) Wm[f] = Wc[f] = Wn[f] = S.w[b][f][w];
       }
       Side<R> topn;  // upper z-face state of cell i-1
       R fzc[5];
       renew_side<R, GR>(topn);
 #pragma unroll
       for (int f = 0; f < 5; ++f) renew(fzc[f]);
-      if (i >= z0) {
+      if (FLAT && i > z0 + 1) {
+        // both z-faces carry the flux of step z0+1
+#pragma unroll
+        for (int f = 0; f < 5; ++f) fzc[f] = st[9 + f];
+      } else if (i >= z0) {
         Side<R> botn;
         recon_cell<R, GR>(2, Wm, Wc, Wn, botn, topn,
                           ph.recon == MHD_RECON_PPH && !(XF && fc));
@@ -596,8 +624,8 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
           const int f = i - 1;
           const double *bg = S.tab[f & 7] + TAB_FACE;
           const FaceBg<R> bgf = {(R)bg[0], (R)bg[1], (R)bg[2], (R)bg[3]};
-          const Side<R> topk = {st[0], st[1], st[2], st[3], st[4],
-                                st[5], st[6], st[7], st[8]};
+          Side<R> topk = {st[0], st[1], st[2], st[3], st[4], st[5], st[6], st[7], st[8]};
+          if (FLAT) topk = topn;
           R fz[7];
           face_flux<R, GR>(XF && (fk | fc) != 0, topk, botn, (R)bzf, bgf, (R)ph.gamma,
                            (R)ph.igm1, ph.xi_mode, (R)ph.mach_cut, (R)ph.imach_cut, fz);
@@ -609,6 +637,11 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
           S.zey[b][e] = -fz[5];  // z-face E_y = -F_z[B_x]
           S.zex[b][e] = fz[6];   // z-face E_x = +F_z[B_y]
           S.zm[b][e] = fz[0];
+          if (FLAT) {
+            S.zey[pb][e] = -fz[5];
+            S.zex[pb][e] = fz[6];
+            S.zm[pb][e] = fz[0];
+          }
         }
       }
       // cells of plane i-2: their flux divergence, and the values of the update
@@ -634,7 +667,7 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
       }
 #pragma unroll
       for (int f = 0; f < PRE_N; ++f) renew(pre[f]);
-      if (i <= z1) {
+      if (!FLAT && i <= z1) {
         int mirn;
         const int kn = zsource(ph, i + 1, mirn);
         request_cell(ph, p, tile_off(ph, t), kn, pre);
@@ -758,7 +791,7 @@ __device__ __forceinline__ void xedge_step(const StageArgs &A, StageLds<R, GR, X
   }
   st[6] = ey_n;
 }
-template <typename R, bool GR, bool XF>
+template <typename R, bool GR, bool XF, bool FLAT>
 __device__ __forceinline__ void xface_step(const StageArgs &A, StageLds<R, GR, XF> &S,
                                            const StageTile &t, int i, R (&st)[XST_N],
                                            double (&pre)[XPRE_N]) {
@@ -771,7 +804,7 @@ __device__ __forceinline__ void xface_step(const StageArgs &A, StageLds<R, GR, X
   const int b = i & 1, pb = b ^ 1;
   const StageIdx ix = idx_rows(t.tid);
   const int e = ix.e;
-  if (i >= z0 && i <= z1 + 1) {
+  if (i >= z0 && i <= (FLAT ? z1 : z1 + 1)) {
     st[3] = st[0];
     st[4] = st[1];
     st[5] = st[2];
@@ -791,6 +824,11 @@ __device__ __forceinline__ void xface_step(const StageArgs &A, StageLds<R, GR, X
     S.xez[b][e] = -fx[5];  // x-face E_z = -F_x[B_y]
     st[0] = fx[6];       // x-face E_y = +F_x[B_z]
     st[1] = fx[0];
+    if (FLAT) {
+      st[3] = st[0];
+      st[4] = st[1];
+      st[5] = st[2];
+    }
   }
   // the face fields the next step updates
 #pragma unroll
@@ -846,7 +884,7 @@ __device__ __forceinline__ void yedge_step(const StageArgs &A, StageLds<R, GR, X
                             st[2], ym_l);
   }
 }
-template <typename R, bool GR, bool XF>
+template <typename R, bool GR, bool XF, bool FLAT>
 __device__ __forceinline__ void yface_step(const StageArgs &A, StageLds<R, GR, XF> &S,
                                            const StageTile &t, int i, R (&st)[YST_N]) {
   constexpr int NF = Cfg<R, GR>::NF;
@@ -855,7 +893,7 @@ __device__ __forceinline__ void yface_step(const StageArgs &A, StageLds<R, GR, X
   const int b = i & 1, pb = b ^ 1;
   const StageIdx ix = idx_cols(t.tid);
   const int e = ix.e;
-  if (i >= z0 && i <= z1 + 1) {
+  if (i >= z0 && i <= (FLAT ? z1 : z1 + 1)) {
     st[5] = st[0];
     st[6] = st[2];
     st[7] = st[3];
@@ -878,12 +916,17 @@ __device__ __forceinline__ void yface_step(const StageArgs &A, StageLds<R, GR, X
     st[0] = -fy[5];     // y-face E_x = -F_y[B_z]
     st[1] = fy[6];
     st[2] = fy[0];
+    if (FLAT) {
+      st[5] = st[0];
+      st[6] = st[2];
+      st[7] = st[3];
+    }
   }
 }
 
 // March of the face waves.  FP64: x-faces and y-faces in waves of their own
 // (DO_X or DO_Y); FP32: both in one wave.
-template <typename R, bool GR, bool XF, bool DO_X, bool DO_Y>
+template <typename R, bool GR, bool XF, bool FLAT, bool DO_X, bool DO_Y>
 __device__ __forceinline__ void face_steps(const StageArgs &args, StageLds<R, GR, XF> &S,
                                            const StageTile &t, const RingCell &rc, double cdt, int wv, int lane,
                                            int &bad) {
@@ -905,15 +948,17 @@ __device__ __forceinline__ void face_steps(const StageArgs &args, StageLds<R, GR
   double tab = 0.0;
   if (DO_X && wv == 0) tab = table_request(args.ph, args.p, z0 - 1, lane);
   for (int i = z0 - 2; i <= z1 + 3; ++i) {
+    if (skip_step<FLAT>(i, z0)) continue;
     const StageArgs &A = stage_args_view();
-    if (FIRST && RING && i <= z1 + 1) ring_step<R, GR, XF>(A, S, rc, i, rpre, bad);
+    const bool ring = RING && i <= (FLAT ? z0 - 1 : z1 + 1);
+    if (FIRST && ring) ring_step<R, GR, XF, FLAT>(A, S, rc, i, rpre, bad);
     if (DO_X) xedge_step<R, GR, XF>(A, S, t, cdt, i, xst, pre);
     if (DO_Y) yedge_step<R, GR, XF>(A, S, t, i, yst);
     if (DO_X && wv == 0 && lane < TAB_N) S.tab[(i + 1) & 7][lane] = tab;
-    if (!FIRST && RING && i <= z1 + 1) ring_step<R, GR, XF>(A, S, rc, i, rpre, bad);
-    if (DO_X) xface_step<R, GR, XF>(A, S, t, i, xst, pre);
-    if (DO_Y) yface_step<R, GR, XF>(A, S, t, i, yst);
-    if (RING && i <= z1) ring_request(A.ph, A.p, rc, i + 1, rpre);
+    if (!FIRST && ring) ring_step<R, GR, XF, FLAT>(A, S, rc, i, rpre, bad);
+    if (DO_X) xface_step<R, GR, XF, FLAT>(A, S, t, i, xst, pre);
+    if (DO_Y) yface_step<R, GR, XF, FLAT>(A, S, t, i, yst);
+    if (RING && !FLAT && i <= z1) ring_request(A.ph, A.p, rc, i + 1, rpre);
     renew(tab);
     if (DO_X && wv == 0) tab = table_request(A.ph, A.p, min(i + 2, z1 + 1), lane);
     __syncthreads();
@@ -923,13 +968,9 @@ __device__ __forceinline__ void face_steps(const StageArgs &args, StageLds<R, GR
 // XF: the optional features of a stage (forcing modes, shock-flattening
 // flags, species mass fluxes); the variant without them carries none of
 // their code, pointers or registers.
-template <typename R, bool GR, bool XF>
-__global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void stage_kernel(
-    StageArgs args) {
-  const Phys &ph = args.ph;
+template <typename R, bool GR, bool XF, bool FLAT>
+__device__ __forceinline__ void stage_block(const StageArgs &args, StageLds<R, GR, XF> &S) {
   const StagePtrs &p = args.p;
-  static_assert(sizeof(MlpLds) % 16 == 0, "MlpLds is copied in 16-byte words");
-  __shared__ StageLds<R, GR, XF> S;
 
   // the first four waves are the columns', the others the faces'; the role
   // is the same for every lane of a wave
@@ -988,17 +1029,21 @@ __global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void st
     // the first plane's table row; the face waves bring one a step
     if (role == 1 && wv == 0) {
       const double v = table_request(ph, A.p, z0 - 2, tid & 63);
-      if ((tid & 63) < TAB_N) S.tab[(z0 - 2) & 7][tid & 63] = v;
+      if ((tid & 63) < TAB_N) {
+        S.tab[(z0 - 2) & 7][tid & 63] = v;
+        if (FLAT)
+          for (int r = 0; r < 8; ++r) S.tab[r][tid & 63] = v;
+      }
     }
     __syncthreads();
     if (role == 0)
-      column_steps<R, GR, XF>(A, S, t, cdt, n);
+      column_steps<R, GR, XF, FLAT>(A, S, t, cdt, n);
     else if constexpr (sizeof(R) == 4)
-      face_steps<R, GR, XF, true, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+      face_steps<R, GR, XF, FLAT, true, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
     else if (role == 1)
-      face_steps<R, GR, XF, true, false>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+      face_steps<R, GR, XF, FLAT, true, false>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
     else
-      face_steps<R, GR, XF, false, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
+      face_steps<R, GR, XF, FLAT, false, true>(A, S, t, rc, cdt, wv, tid & 63, n.bad);
   }
   if (n.bad) atomicOr(p.flags, n.bad);
   if (GR) {
@@ -1030,18 +1075,47 @@ __global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void st
   }
 }
 
+template <typename R, bool GR, bool XF>
+__global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void stage_kernel(
+    StageArgs args) {
+  __shared__ StageLds<R, GR, XF> S;
+  stage_block<R, GR, XF, false>(args, S);
+}
+
+// The stage of a grid of one plane (2D runs): five steps of the march instead
+// of seven, one of them with face solves instead of three, and cells converted
+// once instead of four times.  Bound as stage_kernel is: by the chain of one
+// march where the tiles are few, by FP64 issue where they are many.  A variant
+// of its own because the same tests in stage_kernel cost the other grids 1 to
+// 2 %.  64 x 64 vortex, 20 steps 1062 -> 721 us; 4000 x 3000, 3 steps 28.7 ->
+// 15.8 ms; 1000 x 1010 gas + radiation in split precision, 5 steps 3.59 -> 2.63.
+template <typename R, bool GR, bool XF>
+__global__ __launch_bounds__(stage_threads<R>(), sizeof(R) == 4 ? 4 : 3) void plane_stage_kernel(
+    StageArgs args) {
+  __shared__ StageLds<R, GR, XF> S;
+  stage_block<R, GR, XF, true>(args, S);
+}
+
+static_assert(sizeof(MlpLds) % 16 == 0, "MlpLds is copied in 16-byte words");
 size_t mlp_bytes() { return sizeof(MlpLds); }
+
+// One plane: a reflecting z needs two, so its neighbours along z are itself.
+static bool one_plane(const Phys &ph) { return ph.nz == 1; }
+
+template <typename R, bool GR>
+static auto stage_variant(bool xf, bool flat) -> void (*)(StageArgs) {
+  if (flat) return xf ? plane_stage_kernel<R, GR, true> : plane_stage_kernel<R, GR, false>;
+  return xf ? stage_kernel<R, GR, true> : stage_kernel<R, GR, false>;
+}
 
 template <typename R, bool GR>
 static void launch_stage_g(const Ctx &c, const StagePtrs &p, double a, double b, double cc,
                            double dt_host, dim3 grid) {
-  dim3 block(stage_threads<R>());
-  if (p.fcoef || p.flat || p.mfx || p.mfy || p.mfz)
-    hipLaunchKernelGGL((stage_kernel<R, GR, true>), grid, block, 0, c.stream,
-                       StageArgs{c.ph, p, a, b, cc, dt_host, c.stage_tiles, c.stage_full, c.stage_share});
-  else
-    hipLaunchKernelGGL((stage_kernel<R, GR, false>), grid, block, 0, c.stream,
-                       StageArgs{c.ph, p, a, b, cc, dt_host, c.stage_tiles, c.stage_full, c.stage_share});
+  hipLaunchKernelGGL((stage_variant<R, GR>(p.fcoef || p.flat || p.mfx || p.mfy || p.mfz,
+                                           one_plane(c.ph))),
+                     grid, dim3(stage_threads<R>()), 0, c.stream,
+                     StageArgs{c.ph, p, a, b, cc, dt_host, c.stage_tiles, c.stage_full,
+                               c.stage_share});
 }
 
 template <typename R>
@@ -1058,11 +1132,8 @@ static void launch_stage_t(const Ctx &c, const StagePtrs &p, double a, double b,
 template <typename R>
 static const void *stage_fn(const Ctx &c) {
   const bool xf = c.d.flatten || c.d.nspecies > 0;
-  if (!c.ph.gasrad)
-    return xf ? reinterpret_cast<const void *>(&stage_kernel<R, false, true>)
-              : reinterpret_cast<const void *>(&stage_kernel<R, false, false>);
-  return xf ? reinterpret_cast<const void *>(&stage_kernel<R, true, true>)
-            : reinterpret_cast<const void *>(&stage_kernel<R, true, false>);
+  return c.ph.gasrad ? (const void *)stage_variant<R, true>(xf, one_plane(c.ph))
+                     : (const void *)stage_variant<R, false>(xf, one_plane(c.ph));
 }
 
 int stage_blocks_per_cu(const Ctx &c) {

@@ -897,20 +897,26 @@ static int diffusion_ready(mhd_ctx *h) {
   return MHD_OK;
 }
 
-int mhd_parabolic_dt(mhd_ctx *h, double *dtp_out) {
-  if (!h || !dtp_out) return MHD_ERR_ARG;
-  if (int rc = diffusion_ready(h)) return rc;
+// the parabolic limit of the current state; with start also the start values
+// of a super step from it, in c.diff
+static int parabolic_dt(mhd_ctx *h, double *dtp_out, bool start) {
   mhd::Ctx &c = h->c;
   const int s = c.cur;
   const double *Tg = c.d.eos_guess == MHD_GUESS_PREV_T ? c.T[c.tcur] : nullptr;
   double *slot = c.red + c.red_len - 1;
-  HIPCHK(h, mhd::launch_parabolic_dt(c, c.U[s], c.Bx[s], c.By[s], c.Bz[s], Tg, slot));
+  HIPCHK(h, mhd::launch_parabolic_dt(c, c.U[s], c.Bx[s], c.By[s], c.Bz[s], Tg, slot, start));
   double dtp = 0.0;
   HIPCHK(h, hipMemcpyAsync(&dtp, slot, sizeof(double), hipMemcpyDeviceToHost, c.stream));
   if (int rc = latched(h)) return rc;
   if (!(dtp > 0.0)) return fail(h, MHD_ERR_UNPHYSICAL, "parabolic limit is not positive");
   *dtp_out = dtp;
   return MHD_OK;
+}
+
+int mhd_parabolic_dt(mhd_ctx *h, double *dtp_out) {
+  if (!h || !dtp_out) return MHD_ERR_ARG;
+  if (int rc = diffusion_ready(h)) return rc;
+  return parabolic_dt(h, dtp_out, false);
 }
 
 // RKL2 stage coefficients (Meyer, Balsara & Aslam): b_0 = b_1 = b_2 = 1/3,
@@ -939,9 +945,10 @@ int mhd_diffuse(mhd_ctx *h, double dt, int32_t nsts, int32_t mode, int32_t *nsts
     HIPCHK(h, hipMalloc(&d.M0, bytes));
     HIPCHK(h, hipMalloc(&d.cv0, bytes));
   }
-  if (nsts <= 0) {
+  const bool limit = nsts <= 0;
+  if (limit) {
     double dtp;
-    if (int rc = mhd_parabolic_dt(h, &dtp)) return rc;
+    if (int rc = parabolic_dt(h, &dtp, true)) return rc;
     const int n = 1 + (int)std::floor(0.5 * (std::sqrt(9.0 + 16.0 * dt / dtp) - 1.0));
     if (n > 100000) return fail(h, MHD_ERR_ARG, "dt needs more than 100000 stages");
     nsts = n > 3 ? n : 3;
@@ -951,7 +958,7 @@ int mhd_diffuse(mhd_ctx *h, double dt, int32_t nsts, int32_t mode, int32_t *nsts
   const int tform = mode == MHD_DIFF_TEMP;
   const bool prev_t = c.d.eos_guess == MHD_GUESS_PREV_T;
   const double *Tg = prev_t ? c.T[c.tcur] : nullptr;
-  HIPCHK(h, mhd::launch_diff_init(c, c.U[s], c.Bx[s], c.By[s], c.Bz[s], Tg));
+  if (!limit) HIPCHK(h, mhd::launch_diff_init(c, c.U[s], c.Bx[s], c.By[s], c.Bz[s], Tg));
   // Y_0 is e_int, or T_0 in the temperature form, where the stage values are
   // temperatures themselves and the T buffers only hold T_0
   const double *y0 = tform ? d.T[0] : d.e0;

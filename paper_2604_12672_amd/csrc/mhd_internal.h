@@ -212,9 +212,10 @@ hipError_t launch_diff_stage(const Ctx &c, const double *U, const double *Ta, co
                              double nu, double mut, double gamt, double dt);
 hipError_t launch_diff_finish(const Ctx &c, double *U, const double *ylast, const double *Tlast,
                               int tform, double *Tstore);
+// the parabolic limit; with start also launch_diff_init's values
 hipError_t launch_parabolic_dt(const Ctx &c, const double *U, const double *Bx,
                                const double *By, const double *Bz, const double *Tg,
-                               double *dtp_dev);
+                               double *dtp_dev, bool start);
 // shock flattening (mhd_flatten.hip): the thermal pressure of a stage input
 // into c.shock_p, then the flags from it into c.shock_f
 hipError_t launch_shock_pressure(const Ctx &c, const double *U, const double *Bx,

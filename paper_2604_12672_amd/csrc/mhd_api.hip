@@ -332,7 +332,11 @@ int mhd_init_grid(const mhd_grid_desc *desc, void *hip_stream, mhd_ctx **out) {
     for (int s = 0; s < 2; ++s)
       if ((e = hipMalloc(&c.T[s], sizeof(double) * c.ncell)) != hipSuccess)
         return cleanup(e, "hipMalloc T");
-  c.table_host.assign((size_t)mhd::TAB_N * ph.nzf, 0.0);
+  try {
+    c.table_host.assign((size_t)mhd::TAB_N * ph.nzf, 0.0);
+  } catch (const std::bad_alloc &) {
+    return cleanup(hipErrorOutOfMemory, "host copy of the stage table");
+  }
   if ((e = hipMalloc(&c.table, sizeof(double) * c.table_host.size())) != hipSuccess)
     return cleanup(e, "hipMalloc table");
   if ((e = hipMemsetAsync(c.table, 0, sizeof(double) * c.table_host.size(), c.stream)) !=
@@ -505,12 +509,17 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
     }
     // the split path keeps the coefficients in FP32 (6e-8 of the forcing)
     const bool split = c.d.precision == MHD_PREC_SPLIT;
-    std::vector<float> coef32;
-    if (split) coef32.assign(coef.begin(), coef.end());
-    const void *src = split ? (const void *)coef32.data() : (const void *)coef.data();
-    const size_t bytes = coef.size() * (split ? sizeof(float) : sizeof(double));
+    size_t bytes = coef.size() * sizeof(double);
+    if (split) {
+      // rounded in place: value q goes below value q + 1
+      for (size_t q = 0; q < coef.size(); ++q) {
+        const float v = (float)coef[q];
+        std::memcpy((char *)coef.data() + q * sizeof(float), &v, sizeof(float));
+      }
+      bytes /= 2;
+    }
     if (!c.fcoef) HIPCHK(h, hipMalloc(&c.fcoef, bytes));
-    HIPCHK(h, hipMemcpyAsync(c.fcoef, src, bytes, hipMemcpyHostToDevice, c.stream));
+    HIPCHK(h, hipMemcpyAsync(c.fcoef, coef.data(), bytes, hipMemcpyHostToDevice, c.stream));
     HIPCHK(h, hipStreamSynchronize(c.stream));  // the host tables go out of scope
   } else if (c.fcoef) {
     HIPCHK(h, hipStreamSynchronize(c.stream));

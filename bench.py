@@ -59,7 +59,7 @@ FETCH_FACTOR = 2.0
 WRITE_FACTOR = 1.0
 TRAFFIC_KIB = {
     # digest: {path: (fetch KiB, write KiB) per stage dispatch}
-    "3f5afaf1e16d1e30": {"fp64": (1363793.3, 1115010.8), "split": (1826299.1, 1218578.1)},
+    "1806db662e5ce1af": {"fp64": (1554233.9, 1166144.4), "split": (2542446.4, 1245452.6)},
 }
 
 
@@ -69,7 +69,7 @@ TRAFFIC_KIB = {
 # wave64 instruction per four cycles, 2.4 GHz) they give the launch's
 # instruction-issue floor: the bound the stage kernel actually meets.
 VALU_INSTS = {
-    "3f5afaf1e16d1e30": {"fp64": 863571147, "split": 596439887},
+    "1806db662e5ce1af": {"fp64": 770110151, "split": 621045514},
 }
 VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4.0
 
@@ -77,7 +77,7 @@ VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4.0
 # HBM traffic of diff_stage_kernel (FETCH_SIZE, WRITE_SIZE in KiB per
 # dispatch, averaged over a super step) for the digest of its sources
 RKL2_TRAFFIC_KIB = {
-    "53f859047060231e": {"eint": (501489.2, 397803.5), "temp": (502686.9, 266731.5)},
+    "697a8c678db4ef6e": {"eint": (521642.4, 397803.5), "temp": (504383.5, 266731.5)},
 }
 
 
@@ -188,7 +188,7 @@ def extra_bytes(w, learned):
     """Bytes per zone and stage the stage kernel moves beyond the
     algorithmic ones: the learned guess it reads (the guess kernel's
     output).  Forcing modes cost 120 B per column and launch (the
-    coefficients of the column), under 4 B per zone at 37 planes per
+    coefficients of the column), under 2 B per zone at 64 planes per
     column segment, and are left out."""
     return BYTES_GUESS_ARRAY if (learned and w.T is not None) else 0.0
 

@@ -1552,8 +1552,13 @@ __global__ __launch_bounds__(256) void eos_solve_kernel(
 hipError_t launch_eos_solve(const Ctx &c, const double *rho, const double *e,
                             const double *tguess, long long n, double *T, double *T0,
                             bool stats) {
+  // With the network three rounds of the three resident blocks per CU: each
+  // block stages the 17.5 KB of weights, and with 8192 blocks of a few hundred
+  // samples that was 4 % of the time (4.0 M samples 84.1 -> 78.9 us a call,
+  // 16.8 M 263 -> 260, 0.3 M the same; two rounds 79.4, four 79.6, one 81.5)
+  const long long cap = c.d.eos_guess == MHD_GUESS_MLP ? 9ll * c.cus : 8192;
   long long nb = (n + 255) / 256;
-  nb = nb < 8192 ? nb : 8192;
+  nb = nb < cap ? nb : cap;
   unsigned long long *st = stats ? c.nstats : nullptr;
   if (c.d.eos_guess == MHD_GUESS_MLP)
     hipLaunchKernelGGL(eos_solve_kernel<true>, dim3((unsigned)nb), dim3(256), 0, c.stream, c.ph,

@@ -59,7 +59,7 @@ FETCH_FACTOR = 2.0
 WRITE_FACTOR = 1.0
 TRAFFIC_KIB = {
     # digest: {path: (fetch KiB, write KiB) per stage dispatch}
-    "1806db662e5ce1af": {"fp64": (1554233.9, 1166144.4), "split": (2542446.4, 1245452.6)},
+    "a51c69528243a73c": {"fp64": (1405897.7, 1085419.4), "split": (2425400.5, 1240977.8)},
 }
 
 
@@ -69,7 +69,7 @@ TRAFFIC_KIB = {
 # wave64 instruction per four cycles, 2.4 GHz) they give the launch's
 # instruction-issue floor: the bound the stage kernel actually meets.
 VALU_INSTS = {
-    "1806db662e5ce1af": {"fp64": 770110151, "split": 621045514},
+    "a51c69528243a73c": {"fp64": 770110151, "split": 621045514},
 }
 VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4.0
 

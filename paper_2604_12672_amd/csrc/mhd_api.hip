@@ -179,7 +179,13 @@ void split_stage_work(mhd::Ctx &c) {
   long long best = -1, items = 1;
   for (long long full = 0; full <= (c.d.precision == MHD_PREC_SPLIT ? 0 : tiles / slots); ++full) {
     const long long rest = tiles - full * slots;
-    for (long long segs = 1; segs <= (nz < 64 ? nz : 64); ++segs) {
+    // up to the segments that give every resident block one: few tiles of
+    // many planes need more than 64 (six steps of 14 x 14 x 8192 in FP64: 7.59
+    // ms with 64 segments, 2.35 with the 256 taken here; in split precision
+    // 6.40 and 1.58 with 512)
+    long long most = slots / (rest > 1 ? rest : 1);
+    most = most > 64 ? most : 64;
+    for (long long segs = 1; segs <= (nz < most ? nz : most); ++segs) {
       const long long len = (nz + segs - 1) / segs, n = rest * ((nz + len - 1) / len);
       const long long cost = full * (nz + STAGE_STEPS) +
                              (n + slots - 1) / slots * (len + STAGE_STEPS);

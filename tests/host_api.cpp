@@ -1,0 +1,132 @@
+// The host side of the C ABI (mhd_api.hip) in a program of its own, with the
+// HIP runtime and the kernel launches replaced by stand-ins that move no data
+// to a device.  One command per run; test_host_api.py reads what it prints.
+#include "../paper_2604_12672_amd/csrc/mhd_api.hip"
+
+#include <map>
+
+extern "C" {
+const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "failure"; }
+hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
+hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
+  std::strcpy(p->gcnArchName, "gfx950");
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipMalloc(void **p, size_t) {
+  static size_t next = 4096;
+  *p = reinterpret_cast<void *>(next += 4096);
+  return hipSuccess;
+}
+hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+}
+
+namespace mhd {
+// as the launch bounds and the LDS of the stage kernel leave them
+int stage_blocks_per_cu(const Ctx &c) { return c.d.precision == MHD_PREC_SPLIT ? 2 : 1; }
+int species_segment(const Ctx &) { return 1; }
+int shock_flag_segment(const Ctx &) { return 1; }
+size_t mlp_bytes() { return 17632; }
+hipError_t noalloc_setup(int) { return hipSuccess; }
+hipError_t launch_stage(const Ctx &, const StagePtrs &, double, double, double, double) {
+  return hipSuccess;
+}
+hipError_t launch_signal_speed(const Ctx &, const double *, const double *, const double *,
+                               const double *, const double *, double, double *, double *,
+                               double *) {
+  return hipSuccess;
+}
+hipError_t launch_init_temperature(const Ctx &, const double *, const double *, const double *,
+                                   const double *, const double *, double *) {
+  return hipSuccess;
+}
+hipError_t launch_diagnostics(const Ctx &, const double *, const double *, const double *,
+                              const double *, double *) {
+  return hipSuccess;
+}
+hipError_t launch_zero_walls(const Ctx &, double *) { return hipSuccess; }
+hipError_t launch_mlp_guess(const Ctx &, const double *, const double *, const double *,
+                            const double *, double *, double *, bool, unsigned long long *) {
+  return hipSuccess;
+}
+hipError_t launch_diff_init(const Ctx &, const double *, const double *, const double *,
+                            const double *, const double *) {
+  return hipSuccess;
+}
+hipError_t launch_diff_stage(const Ctx &, const double *, const double *, const double *,
+                             const double *, const double *, const double *, double *, double *,
+                             double *, int, int, double, double, double, double, double) {
+  return hipSuccess;
+}
+hipError_t launch_diff_finish(const Ctx &, double *, const double *, const double *, int,
+                              double *) {
+  return hipSuccess;
+}
+hipError_t launch_parabolic_dt(const Ctx &, const double *, const double *, const double *,
+                               const double *, const double *, double *, bool) {
+  return hipSuccess;
+}
+hipError_t launch_shock_pressure(const Ctx &, const double *, const double *, const double *,
+                                 const double *, const double *, int) {
+  return hipSuccess;
+}
+hipError_t launch_shock_flags(const Ctx &) { return hipSuccess; }
+hipError_t launch_species(const Ctx &, const double *, const double *, const double *, double *,
+                          double, double, double, double, const double *, const uint8_t *) {
+  return hipSuccess;
+}
+hipError_t launch_eos_solve(const Ctx &, const double *, const double *, const double *,
+                            long long, double *, double *, bool) {
+  return hipSuccess;
+}
+hipError_t launch_math_check(hipStream_t, const double *, double *, long long) {
+  return hipSuccess;
+}
+}  // namespace mhd
+
+namespace {
+
+mhd_ctx *grid(long nx, long ny, long nz, int precision, int eos = MHD_EOS_IDEAL) {
+  mhd_grid_desc d;
+  std::memset(&d, 0, sizeof(d));
+  d.nx = (int)nx;
+  d.ny = (int)ny;
+  d.nz = (int)nz;
+  for (int a = 0; a < 3; ++a) d.hi[a] = 1.0;
+  d.eos = eos;
+  d.gamma = 5.0 / 3.0;
+  d.mu = d.rgas = d.arad = 1.0;
+  d.rk_order = 2;
+  d.precision = precision;
+  d.newton_tol = 1e-11;
+  d.newton_maxit = 50;
+  d.mach_cut = 0.6;
+  mhd_ctx *h = nullptr;
+  if (mhd_init_grid(&d, nullptr, &h) != MHD_OK) {
+    std::printf("init failed: %s\n", mhd_last_error(nullptr));
+    std::exit(1);
+  }
+  return h;
+}
+
+// split nx ny nz precision: the stage kernel's work split
+int split(char **v) {
+  mhd_ctx *h = grid(std::atol(v[0]), std::atol(v[1]), std::atol(v[2]), std::atoi(v[3]));
+  std::printf("%d %d %d %d\n", h->c.stage_full, h->c.stage_share, h->c.zseg, h->c.stage_blocks);
+  return mhd_destroy(h);
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+  const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {{"split", {4, split}}};
+  const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
+  if (it == commands.end() || argc - 2 != it->second.first) return 2;
+  return it->second.second(argv + 2);
+}

@@ -1,0 +1,50 @@
+"""The host side of the C ABI on the CPU: mhd_api.hip compiled for the host,
+with the HIP runtime and the kernel launches replaced by stand-ins
+(host_api.cpp).  Needs hipcc."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def api(tmp_path_factory):
+    from paper_2604_12672_amd import build
+    if shutil.which(build.HIPCC) is None and not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not available")
+    d = tmp_path_factory.mktemp("host_api")
+    obj, exe = str(d / "host_api.o"), str(d / "host_api")
+    subprocess.run([build.HIPCC, "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-O1",
+                    "-fPIC", "-std=c++17", "-c", os.path.join(HERE, "host_api.cpp"), "-o", obj], check=True)
+    subprocess.run(["g++", obj, "-o", exe], check=True)
+
+    def run(*args, zseg=None):
+        env = dict(os.environ)
+        env.pop("MHD_ZSEG", None)
+        if zseg is not None:
+            env["MHD_ZSEG"] = str(zseg)
+        return subprocess.run([exe] + [str(a) for a in args], check=True, capture_output=True,
+                              text=True, timeout=60, env=env).stdout.split()
+    return run
+
+
+def split(api, nx, ny, nz, precision, **kw):
+    return dict(zip(("full", "share", "zseg", "blocks"),
+                    map(int, api("split", nx, ny, nz, precision, **kw))))
+
+
+# one to seven tiles with a long z: a march that leaves most of the CUs (256
+# here, one FP64 or two split blocks each) without work takes that much longer
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,ny,nz", [(1, 1, 4096), (1, 1, 8192), (14, 14, 8192), (28, 14, 4096),
+                                      (42, 14, 20000), (98, 14, 6000), (14, 14, 1000003)])
+def test_tall_narrow_grid_fills_the_chip(api, nx, ny, nz, precision):
+    s = split(api, nx, ny, nz, precision)
+    slots = 256 * (1 + precision)
+    tiles = -(-nx // 14) * -(-ny // 14)
+    assert s["full"] == 0
+    assert s["share"] == s["zseg"] <= -(-nz // (slots // tiles))
+    assert s["blocks"] == tiles * -(-nz // s["share"])

@@ -122,10 +122,18 @@ int split(char **v) {
   return mhd_destroy(h);
 }
 
+// segment tiles nz slots extra: planes per segment of the other marches
+int segment(char **v) {
+  std::printf("%d\n", mhd::segment_planes(std::atol(v[0]), std::atoi(v[1]), std::atol(v[2]),
+                                          std::atoi(v[3])));
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
-  const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {{"split", {4, split}}};
+  const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {
+      {"split", {4, split}}, {"segment", {4, segment}}};
   const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
   if (it == commands.end() || argc - 2 != it->second.first) return 2;
   return it->second.second(argv + 2);

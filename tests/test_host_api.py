@@ -48,3 +48,10 @@ def test_tall_narrow_grid_fills_the_chip(api, nx, ny, nz, precision):
     assert s["full"] == 0
     assert s["share"] == s["zseg"] <= -(-nz // (slots // tiles))
     assert s["blocks"] == tiles * -(-nz // s["share"])
+
+
+# the species and flag kernels: the same rule on their tiles and their slots
+@pytest.mark.parametrize("tiles,nz,slots", [(1, 20000, 512), (1, 30000, 1024), (3, 90000, 1024),
+                                            (7, 1000003, 2048)])
+def test_segments_of_few_tiles_fill_the_chip(api, tiles, nz, slots):
+    assert int(api("segment", tiles, nz, slots, 3)[0]) <= -(-nz // (slots // tiles))

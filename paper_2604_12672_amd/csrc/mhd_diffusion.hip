@@ -75,15 +75,18 @@ __global__ __launch_bounds__(256) void diff_init_kernel(
 // neighbours), the tile's plane k with a one-cell ring is staged in LDS
 // (the x and y neighbours), so T and chi are read from HBM about once.  The
 // kernel moves 80 B a cell (72 in the temperature form) and waits on them
-// most of the time (four waves per SIMD, vector pipe 47 % busy): the other
-// values of a plane are requested before its staging and barrier, and short
-// segments keep more blocks in flight (192^3: 159 us a stage with 16 planes
-// and the values loaded at their use, 140 us now).
-constexpr int DTX = 64, DTY = 4;                // tile (256 threads)
+// most of the time: the other values of a plane are requested before its
+// staging and barrier, and short segments keep more blocks in flight (192^3:
+// 159 us a stage with 16 planes and the values loaded at their use, 139 us now).
+// Five waves per SIMD, 96 registers: with one register more, four waves, thin
+// grids, whose blocks move little, took longer than with the values loaded at
+// their use (13 stages of 1 x 100000 x 1: 1.37 ms at their use, 1.44 with four
+// waves, 1.36 with five; 1 x 1 x 200000 4.18, 4.77 and 4.14).  The internal-energy
+// form, which keeps more over the inversion, loads M0 at its use to fit them.
 constexpr int DLX = DTX + 2, DLY = DTY + 2;     // staged plane with its ring
 
 template <bool TF>
-__global__ __launch_bounds__(256) void diff_stage_kernel(
+__global__ __launch_bounds__(DTX * DTY, 5) void diff_stage_kernel(
     Phys ph, DiffParams dp, const double *__restrict__ U, const double *__restrict__ Ta,
     const double *__restrict__ chia, const double *__restrict__ y0,
     const double *__restrict__ y1, const double *__restrict__ y2, double *__restrict__ M0,
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
       if (!first) {
         v1 = TF ? tc : y1[q];
         v2 = y2[q];
-        m0 = M0[q];
+        if (TF) m0 = M0[q];
       }
     }
     sT[ty + 1][tx + 1] = tc;
@@ -171,7 +174,8 @@ __global__ __launch_bounds__(256) void diff_stage_kernel(
         M0[q] = M;
         v = v0 + mut * dt * M;
       } else {
-        v = mu * v1 + nu * v2 + (1.0 - mu - nu) * v0 + mut * dt * M + gamt * dt * m0;
+        v = mu * v1 + nu * v2 + (1.0 - mu - nu) * v0 + mut * dt * M +
+            gamt * dt * (TF ? m0 : M0[q]);
       }
       yn[q] = v;
       double t = v;
@@ -303,21 +307,13 @@ hipError_t launch_diff_init(const Ctx &c, const double *U, const double *Bx, con
   return hipGetLastError();
 }
 
-// Planes per block: eight where that makes 16 blocks per CU (four rounds of
-// the four resident ones), else four.  A super step of 20 stages: 256^3 8.01
-// ms with eight, 8.15 with four (8.22 with sixteen); 192^3 3.54 and 3.50;
-// 96 x 90 x 101 0.83 and 0.72 (1.23 with sixteen).
-static int diff_segment(long long tiles, const Ctx &c) {
-  return tiles * ((c.ph.nz + 7) / 8) >= 16ll * c.cus ? 8 : 4;
-}
-
 hipError_t launch_diff_stage(const Ctx &c, const double *U, const double *Ta, const double *chia,
                              const double *y0, const double *y1, const double *y2, double *yn,
                              double *Tb, double *chib, int tform, int first, double mu,
                              double nu, double mut, double gamt, double dt) {
   const DiffBufs &d = c.diff;
   const int tiles = ((c.ph.nx + DTX - 1) / DTX) * ((c.ph.ny + DTY - 1) / DTY);
-  const int zseg = diff_segment(tiles, c);
+  const int zseg = diff_segment(c.ph, c.cus);
   const dim3 grid(tiles * ((c.ph.nz + zseg - 1) / zseg));
   if (tform)
     hipLaunchKernelGGL(diff_stage_kernel<true>, grid, dim3(256), 0, c.stream,

@@ -111,6 +111,22 @@ inline int segment_planes(long long tiles, int nz, long long slots, int extra) {
   return len;
 }
 
+// Planes per block of the diffusion stage kernel, a DTX x DTY column tile:
+// eight where that makes 16 blocks per CU (three rounds of the five resident
+// ones), else four.  A super step of 20 stages: 256^3 8.01 ms with eight, 8.15
+// with four (8.22 with sixteen); 192^3 3.54 and 3.50; 96 x 90 x 101 0.83 and
+// 0.72 (1.23 with sixteen).  Where three quarters of a tile's lanes own no cell
+// a block moves little and its start weighs more: sixteen where that makes 32
+// blocks per CU (13 stages of 1 x 1 x 200000 4.24 to 4.30 ms with eight, 4.14 to
+// 4.20 with sixteen; of 1 x 1 x 60000, below the line, 1.43 and 1.46).
+constexpr int DTX = 64, DTY = 4;
+inline int diff_segment(const Phys &ph, int cus) {
+  const long long tiles = (long long)((ph.nx + DTX - 1) / DTX) * ((ph.ny + DTY - 1) / DTY);
+  auto blocks = [&](int z) { return tiles * (((long long)ph.nz + z - 1) / z); };
+  if ((long long)ph.nx * ph.ny * 4 <= tiles * (DTX * DTY) && blocks(16) >= 32ll * cus) return 16;
+  return blocks(8) >= 16ll * cus ? 8 : 4;
+}
+
 struct Ctx {
   mhd_grid_desc d;
   Phys ph;

@@ -129,11 +129,21 @@ int segment(char **v) {
   return 0;
 }
 
+// dsegment nx ny nz: planes per block of the diffusion stage kernel
+int dsegment(char **v) {
+  mhd::Phys ph{};
+  ph.nx = std::atoi(v[0]);
+  ph.ny = std::atoi(v[1]);
+  ph.nz = std::atoi(v[2]);
+  std::printf("%d\n", mhd::diff_segment(ph, 256));
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {
-      {"split", {4, split}}, {"segment", {4, segment}}};
+      {"split", {4, split}}, {"segment", {4, segment}}, {"dsegment", {3, dsegment}}};
   const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
   if (it == commands.end() || argc - 2 != it->second.first) return 2;
   return it->second.second(argv + 2);

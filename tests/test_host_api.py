@@ -55,3 +55,13 @@ def test_tall_narrow_grid_fills_the_chip(api, nx, ny, nz, precision):
                                             (7, 1000003, 2048)])
 def test_segments_of_few_tiles_fill_the_chip(api, tiles, nz, slots):
     assert int(api("segment", tiles, nz, slots, 3)[0]) <= -(-nz // (slots // tiles))
+
+
+# few lanes of a tile with a cell: the 16 planes the kernel had for every grid,
+# where they leave enough blocks
+@pytest.mark.parametrize("nx,ny,nz,planes", [
+    (1, 1, 131072, 16), (1, 1, 131056, 8), (7, 5, 100000, 16), (16, 4, 131072, 16),
+    (17, 4, 131072, 8), (1, 1, 32768, 8), (1, 1, 32760, 4), (192, 192, 192, 4), (256, 256, 256, 8),
+    (64, 4, 1000000, 8)])
+def test_planes_of_a_diffusion_block(api, nx, ny, nz, planes):
+    assert int(api("dsegment", nx, ny, nz)[0]) == planes

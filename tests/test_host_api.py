@@ -50,6 +50,14 @@ def test_tall_narrow_grid_fills_the_chip(api, nx, ny, nz, precision):
     assert s["blocks"] == tiles * -(-nz // s["share"])
 
 
+# a launch holds fewer than 2^32 threads; a line of these cells has more tiles
+# than that allows blocks of 512 threads
+@pytest.mark.parametrize("nx,ny,nz,zseg", [(120000000, 1, 1, None), (536870911, 1, 2, None),
+                                           (1, 117441000, 3, None), (30000000, 1, 4, 1)])
+def test_launch_of_very_many_tiles(api, nx, ny, nz, zseg):
+    assert split(api, nx, ny, nz, 1, zseg=zseg)["blocks"] * 512 < 2 ** 32
+
+
 # the species and flag kernels: the same rule on their tiles and their slots
 @pytest.mark.parametrize("tiles,nz,slots", [(1, 20000, 512), (1, 30000, 1024), (3, 90000, 1024),
                                             (7, 1000003, 2048)])

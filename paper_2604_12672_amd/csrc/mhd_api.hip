@@ -208,17 +208,28 @@ void split_stage_work(mhd::Ctx &c) {
   c.stage_tiles = (int)tiles;
   // FP64: the resident blocks take the items in turn; split precision: a block
   // for each (10 % faster), as far as the threads of a launch (below 2^32) go
-  const long long most = c.d.precision == MHD_PREC_SPLIT ? 4294967295ll / (2 * mhd::NTHREADS) : slots;
+  const long long most =
+      c.d.precision == MHD_PREC_SPLIT ? 4294967295ll / (2 * mhd::NTHREADS) : slots;
   c.stage_blocks = (int)(c.stage_full > 0 ? slots : items < most ? items : most);
   c.zseg = c.stage_full > 0 ? (int)nz : c.stage_share;
 }
 
-// the stage kernel's table to the device (synchronises)
-int upload_table(mhd_ctx *h) {
+// A changed copy of the stage kernel's table to the device (synchronises); the
+// context's own takes its values only then, so that a call that fails leaves
+// none for the next one to upload.
+int upload_table(mhd_ctx *h, std::vector<double> &table) {
   mhd::Ctx &c = h->c;
-  HIPCHK(h, hipMemcpyAsync(c.table, c.table_host.data(), sizeof(double) * c.table_host.size(),
+  HIPCHK(h, hipMemcpyAsync(c.table, table.data(), sizeof(double) * table.size(),
                            hipMemcpyHostToDevice, c.stream));
   HIPCHK(h, hipStreamSynchronize(c.stream));
+  c.table_host.swap(table);
+  return MHD_OK;
+}
+
+// the coefficients of the forcing to the device (synchronises)
+int upload_coefficients(mhd_ctx *h, void *dst, const void *src, size_t bytes) {
+  HIPCHK(h, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, h->c.stream));
+  HIPCHK(h, hipStreamSynchronize(h->c.stream));
   return MHD_OK;
 }
 
@@ -436,12 +447,13 @@ int mhd_set_background(mhd_ctx *h, const double *w_cc, const double *w_fz) {
     for (int k = 0; k < nzf; ++k)
       if (!std::isfinite(w_fz[f * nzf + k])) return fail(h, MHD_ERR_ARG, "background not finite");
   }
+  std::vector<double> table = c.table_host;
   for (int f = 0; f < 4; ++f) {
-    for (int k = 0; k < nz; ++k) c.table_host[(size_t)k * mhd::TAB_N + f] = w_cc[f * nz + k];
+    for (int k = 0; k < nz; ++k) table[(size_t)k * mhd::TAB_N + f] = w_cc[f * nz + k];
     for (int k = 0; k < nzf; ++k)
-      c.table_host[(size_t)k * mhd::TAB_N + mhd::TAB_FACE + f] = w_fz[f * nzf + k];
+      table[(size_t)k * mhd::TAB_N + mhd::TAB_FACE + f] = w_fz[f * nzf + k];
   }
-  return upload_table(h);
+  return upload_table(h, table);
 }
 
 int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_t nmodes) {
@@ -462,8 +474,8 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
     for (int k = 0; k < c.ph.nz; ++k)
       if (!std::isfinite(heat[k])) return fail(h, MHD_ERR_ARG, "heating must be finite");
   }
-  for (int k = 0; k < c.ph.nz; ++k)
-    c.table_host[(size_t)k * mhd::TAB_N + 4] = heat ? heat[k] : 0.0;
+  std::vector<double> table = c.table_host;
+  for (int k = 0; k < c.ph.nz; ++k) table[(size_t)k * mhd::TAB_N + 4] = heat ? heat[k] : 0.0;
   if (nmodes > 0) {
     // f(x) = sum_m a_m cos(alpha_m(x, y) + 2 pi k_z,m Z), alpha_m = 2 pi
     // (k_x X + k_y Y) + phi_m, X = (x - lo)/L at cell centres.  With
@@ -509,7 +521,7 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
     }
     for (int k = 0; k < nz; ++k) {
       const double Z = (k + 0.5) / nz;
-      double *zb = c.table_host.data() + (size_t)k * mhd::TAB_N + 5;
+      double *zb = table.data() + (size_t)k * mhd::TAB_N + 5;
       zb[0] = 1.0;
       zb[1] = std::cos(pi2 * Z);
       zb[2] = std::sin(pi2 * Z);
@@ -527,15 +539,20 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
       }
       bytes /= 2;
     }
-    if (!c.fcoef) HIPCHK(h, hipMalloc(&c.fcoef, bytes));
-    HIPCHK(h, hipMemcpyAsync(c.fcoef, coef.data(), bytes, hipMemcpyHostToDevice, c.stream));
-    HIPCHK(h, hipStreamSynchronize(c.stream));  // the host tables go out of scope
-  } else if (c.fcoef) {
-    HIPCHK(h, hipStreamSynchronize(c.stream));
-    (void)hipFree(c.fcoef);
-    c.fcoef = nullptr;
+    void *dev = c.fcoef;
+    if (!dev) HIPCHK(h, hipMalloc(&dev, bytes));
+    int rc = upload_coefficients(h, dev, coef.data(), bytes);
+    if (rc == MHD_OK) rc = upload_table(h, table);
+    if (rc == MHD_OK)
+      c.fcoef = dev;
+    else if (!c.fcoef)
+      (void)hipFree(dev);
+    return rc;
   }
-  return upload_table(h);
+  if (int rc = upload_table(h, table)) return rc;
+  (void)hipFree(c.fcoef);
+  c.fcoef = nullptr;
+  return MHD_OK;
 }
 
 int mhd_set_state(mhd_ctx *h, const double *U, const double *Bx, const double *By,

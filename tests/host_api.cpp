@@ -5,6 +5,16 @@
 
 #include <map>
 
+namespace {
+// the k-th call from now of a kind that fails (0: none)
+long fail_malloc = 0, fail_copy = 0, fail_sync = 0;
+bool fails(long &k) { return k > 0 && --k == 0; }
+// device allocations of up to 1 MB hold what is copied into them; the others
+// are an address only
+std::map<void *, size_t> held;
+long live = 0;
+}  // namespace
+
 extern "C" {
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "failure"; }
 hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
@@ -14,17 +24,30 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
-hipError_t hipMalloc(void **p, size_t) {
+hipError_t hipMalloc(void **p, size_t bytes) {
   static size_t next = 4096;
-  *p = reinterpret_cast<void *>(next += 4096);
+  *p = nullptr;
+  if (fails(fail_malloc)) return hipErrorOutOfMemory;
+  *p = bytes <= 1 << 20 ? std::calloc(bytes, 1) : reinterpret_cast<void *>(next += 4096);
+  if (bytes <= 1 << 20) held[*p] = bytes;
+  ++live;
   return hipSuccess;
 }
-hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipFree(void *p) {
+  if (p) --live;
+  if (held.erase(p)) std::free(p);
+  return hipSuccess;
+}
 hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return hipSuccess; }
-hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) {
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t) {
+  if (fails(fail_copy)) return hipErrorUnknown;
+  if (kind == hipMemcpyHostToDevice && held.count(dst)) {
+    if (held[dst] < bytes) std::abort();
+    std::memcpy(dst, src, bytes);
+  }
   return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return fails(fail_sync) ? hipErrorUnknown : hipSuccess; }
 }
 
 namespace mhd {
@@ -139,11 +162,63 @@ int dsegment(char **v) {
   return 0;
 }
 
+// A call that fails at its k-th `what`, for every k until none is left: the
+// sources and the background on the device are those of before the call, also
+// after the next successful call has uploaded them again.
+int sources(char **v) {
+  const std::string what = v[0];
+  long &counter = what == "malloc" ? fail_malloc : what == "copy" ? fail_copy : fail_sync;
+  const int nz = 4;
+  const double heat1[nz] = {1, 2, 3, 4}, heat2[nz] = {5, 6, 7, 8};
+  double bg1[4 * nz], bg2[4 * nz], mode[7] = {1, 0, 0, 0.1, 0.2, 0.3, 0.4};
+  for (int i = 0; i < 4 * nz; ++i) {
+    bg1[i] = 10 + i;
+    bg2[i] = 50 + i;
+  }
+  long failed = 0, wrong = 0;
+  for (int call = 0; call < 2; ++call) {
+    for (long k = 1;; ++k) {
+      mhd_ctx *h = grid(8, 6, nz, MHD_PREC_FP64);
+      const double *table = h->c.table;
+      auto differs = [&](const double *heat, const double *bg) {
+        for (int z = 0; z < nz; ++z) {
+          if (table[z * mhd::TAB_N + 4] != heat[z]) return true;
+          for (int f = 0; f < 4; ++f)
+            if (table[z * mhd::TAB_N + f] != bg[f * nz + z] ||
+                table[z * mhd::TAB_N + mhd::TAB_FACE + f] != bg[f * nz + z])
+              return true;
+        }
+        return false;
+      };
+      if (mhd_set_background(h, bg1, bg1) || mhd_set_sources(h, heat1, nullptr, 0)) return 1;
+      const long before = live;
+      counter = k;
+      const int rc = call ? mhd_set_background(h, bg2, bg2) : mhd_set_sources(h, heat2, mode, 1);
+      const bool reached = counter == 0;
+      counter = 0;
+      if (!reached) {
+        wrong += rc != MHD_OK || differs(call ? heat1 : heat2, call ? bg2 : bg1);
+        mhd_destroy(h);
+        break;
+      }
+      ++failed;
+      wrong += rc == MHD_OK || h->c.fcoef || live != before;
+      // the call that is not the failed one, with its values of before
+      if (call ? mhd_set_sources(h, heat1, nullptr, 0) : mhd_set_background(h, bg1, bg1)) return 1;
+      wrong += differs(heat1, bg1);
+      mhd_destroy(h);
+    }
+  }
+  std::printf("%ld %ld %ld\n", failed, wrong, live);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {
-      {"split", {4, split}}, {"segment", {4, segment}}, {"dsegment", {3, dsegment}}};
+      {"split", {4, split}}, {"segment", {4, segment}}, {"dsegment", {3, dsegment}},
+      {"sources", {1, sources}}};
   const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
   if (it == commands.end() || argc - 2 != it->second.first) return 2;
   return it->second.second(argv + 2);

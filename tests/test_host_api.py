@@ -73,3 +73,11 @@ def test_segments_of_few_tiles_fill_the_chip(api, tiles, nz, slots):
     (64, 4, 1000000, 8)])
 def test_planes_of_a_diffusion_block(api, nx, ny, nz, planes):
     assert int(api("dsegment", nx, ny, nz)[0]) == planes
+
+
+# the background and the sources share one table: a call that fails leaves no
+# half of its own values for the next one to upload, and no buffer behind
+@pytest.mark.parametrize("what,times", [("malloc", 1), ("copy", 3), ("sync", 3)])
+def test_failed_call_leaves_sources_and_background(api, what, times):
+    failed, wrong, live = map(int, api("sources", what))
+    assert (failed, wrong, live) == (times, 0, 0)

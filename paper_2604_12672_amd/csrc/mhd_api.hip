@@ -30,6 +30,16 @@ int hip_fail(mhd_ctx *h, hipError_t e, const char *what) {
   return fail(h, MHD_ERR_HIP, m);
 }
 
+// a failed host allocation: no exception may leave the C functions
+int out_of_memory(mhd_ctx *h) {
+  try {
+    h->c.err = "out of host memory";
+  } catch (const std::bad_alloc &) {
+    h->c.err.clear();
+  }
+  return MHD_ERR_HIP;
+}
+
 #define HIPCHK(h, call)                                      \
   do {                                                       \
     hipError_t e_ = (call);                                  \
@@ -436,7 +446,7 @@ const char *mhd_last_error(const mhd_ctx *h) {
   return h->c.err.c_str();
 }
 
-int mhd_set_background(mhd_ctx *h, const double *w_cc, const double *w_fz) {
+int mhd_set_background(mhd_ctx *h, const double *w_cc, const double *w_fz) try {
   if (!h) return MHD_ERR_ARG;
   mhd::Ctx &c = h->c;
   if (!w_cc || !w_fz) return fail(h, MHD_ERR_ARG, "background arrays must not be NULL");
@@ -454,9 +464,11 @@ int mhd_set_background(mhd_ctx *h, const double *w_cc, const double *w_fz) {
       table[(size_t)k * mhd::TAB_N + mhd::TAB_FACE + f] = w_fz[f * nzf + k];
   }
   return upload_table(h, table);
+} catch (const std::bad_alloc &) {
+  return out_of_memory(h);
 }
 
-int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_t nmodes) {
+int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_t nmodes) try {
   if (!h) return MHD_ERR_ARG;
   mhd::Ctx &c = h->c;
   if (nmodes < 0 || nmodes > MHD_MAX_FMODES || (nmodes > 0 && !fmodes))
@@ -553,6 +565,8 @@ int mhd_set_sources(mhd_ctx *h, const double *heat, const double *fmodes, int32_
   (void)hipFree(c.fcoef);
   c.fcoef = nullptr;
   return MHD_OK;
+} catch (const std::bad_alloc &) {
+  return out_of_memory(h);
 }
 
 int mhd_set_state(mhd_ctx *h, const double *U, const double *Bx, const double *By,
@@ -817,7 +831,7 @@ int mhd_diagnostics(mhd_ctx *h, mhd_diag *out) {
 }
 
 int mhd_set_eos_mlp(mhd_ctx *h, const float *w1, const float *b1, const uint16_t *w2,
-                    const float *b2, const uint16_t *w3, float b3, const double *norm) {
+                    const float *b2, const uint16_t *w3, float b3, const double *norm) try {
   if (!h) return MHD_ERR_ARG;
   mhd::Ctx &c = h->c;
   if (c.d.eos_guess != MHD_GUESS_MLP)
@@ -885,6 +899,8 @@ int mhd_set_eos_mlp(mhd_ctx *h, const float *w1, const float *b1, const uint16_t
   c.t0_current = false;
   c.p_current = false;
   return MHD_OK;
+} catch (const std::bad_alloc &) {
+  return out_of_memory(h);
 }
 
 int mhd_eos_solve(mhd_ctx *h, const double *rho, const double *e, const double *T_guess,

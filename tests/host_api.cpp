@@ -8,12 +8,21 @@
 namespace {
 // the k-th call from now of a kind that fails (0: none)
 long fail_malloc = 0, fail_copy = 0, fail_sync = 0;
+long fail_new = 0;
 bool fails(long &k) { return k > 0 && --k == 0; }
 // device allocations of up to 1 MB hold what is copied into them; the others
 // are an address only
 std::map<void *, size_t> held;
 long live = 0;
 }  // namespace
+
+void *operator new(size_t n) {
+  if (fails(fail_new)) throw std::bad_alloc();
+  if (void *p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "failure"; }
@@ -29,7 +38,10 @@ hipError_t hipMalloc(void **p, size_t bytes) {
   *p = nullptr;
   if (fails(fail_malloc)) return hipErrorOutOfMemory;
   *p = bytes <= 1 << 20 ? std::calloc(bytes, 1) : reinterpret_cast<void *>(next += 4096);
+  const long k = fail_new;  // not of the map's own
+  fail_new = 0;
   if (bytes <= 1 << 20) held[*p] = bytes;
+  fail_new = k;
   ++live;
   return hipSuccess;
 }
@@ -115,7 +127,7 @@ hipError_t launch_math_check(hipStream_t, const double *, double *, long long) {
 
 namespace {
 
-mhd_ctx *grid(long nx, long ny, long nz, int precision, int eos = MHD_EOS_IDEAL) {
+mhd_grid_desc desc(long nx, long ny, long nz, int precision, int eos) {
   mhd_grid_desc d;
   std::memset(&d, 0, sizeof(d));
   d.nx = (int)nx;
@@ -130,6 +142,11 @@ mhd_ctx *grid(long nx, long ny, long nz, int precision, int eos = MHD_EOS_IDEAL)
   d.newton_tol = 1e-11;
   d.newton_maxit = 50;
   d.mach_cut = 0.6;
+  return d;
+}
+
+mhd_ctx *grid(long nx, long ny, long nz, int precision) {
+  const mhd_grid_desc d = desc(nx, ny, nz, precision, MHD_EOS_IDEAL);
   mhd_ctx *h = nullptr;
   if (mhd_init_grid(&d, nullptr, &h) != MHD_OK) {
     std::printf("init failed: %s\n", mhd_last_error(nullptr));
@@ -213,12 +230,51 @@ int sources(char **v) {
   return 0;
 }
 
+// Every host allocation of a call fails in turn: calls, allocations, calls that
+// threw, calls that did not report it, device buffers left.
+int host_memory(char **) {
+  const int nz = 4;
+  const double heat[nz] = {1, 2, 3, 4}, bg[4 * nz] = {0.0}, mode[7] = {1, 0, 0, 0.1, 0.2, 0.3, 0.4};
+  const std::vector<float> w1(128, 0.5f), b(64, 0.5f);
+  const std::vector<uint16_t> w2(64 * 64, 0), w3(64, 0);
+  const double norm[6] = {0, 1, 0, 1, 0, 1};
+  long reached = 0, thrown = 0, missed = 0;
+  const int calls = 5;
+  for (int call = 0; call < calls; ++call) {
+    for (long k = 1;; ++k) {
+      mhd_ctx *h = nullptr;
+      mhd_grid_desc d = desc(8, 6, nz, call == 2 ? MHD_PREC_SPLIT : MHD_PREC_FP64, MHD_EOS_GASRAD);
+      if (call == 4) d.eos_guess = MHD_GUESS_MLP;
+      if (call && mhd_init_grid(&d, nullptr, &h)) return 1;
+      int rc = MHD_OK;
+      fail_new = k;
+      try {
+        rc = call == 0   ? mhd_init_grid(&d, nullptr, &h)
+             : call == 1 ? mhd_set_background(h, bg, bg)
+             : call <= 3 ? mhd_set_sources(h, heat, mode, 1)
+                         : mhd_set_eos_mlp(h, w1.data(), b.data(), w2.data(), b.data(), w3.data(),
+                                           0.5f, norm);
+      } catch (const std::bad_alloc &) {
+        ++thrown;
+      }
+      const bool hit = fail_new == 0;
+      fail_new = 0;
+      reached += hit;
+      missed += hit ? rc == MHD_OK : rc != MHD_OK;
+      mhd_destroy(h);
+      if (!hit) break;
+    }
+  }
+  std::printf("%d %ld %ld %ld %ld\n", calls, reached, thrown, missed, live);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {
       {"split", {4, split}}, {"segment", {4, segment}}, {"dsegment", {3, dsegment}},
-      {"sources", {1, sources}}};
+      {"sources", {1, sources}}, {"host_memory", {0, host_memory}}};
   const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
   if (it == commands.end() || argc - 2 != it->second.first) return 2;
   return it->second.second(argv + 2);

@@ -81,3 +81,11 @@ def test_planes_of_a_diffusion_block(api, nx, ny, nz, planes):
 def test_failed_call_leaves_sources_and_background(api, what, times):
     failed, wrong, live = map(int, api("sources", what))
     assert (failed, wrong, live) == (times, 0, 0)
+
+
+# creating a grid, the background, the sources (split precision and FP64) and
+# the network: no exception leaves the C functions
+def test_failed_host_allocation_is_an_error_code(api):
+    calls, reached, thrown, missed, live = map(int, api("host_memory"))
+    assert reached >= 2 * calls
+    assert (thrown, missed, live) == (0, 0, 0)

@@ -986,15 +986,19 @@ int mhd_diffuse(mhd_ctx *h, double dt, int32_t nsts, int32_t mode, int32_t *nsts
   if (nsts > 100000) return fail(h, MHD_ERR_ARG, "nsts too large");
   mhd::DiffBufs &d = c.diff;
   if (!d.e0) {
-    const size_t bytes = sizeof(double) * c.ncell;
-    HIPCHK(h, hipMalloc(&d.e0, bytes));
-    for (int i = 0; i < 3; ++i) HIPCHK(h, hipMalloc(&d.y[i], bytes));
-    for (int i = 0; i < 2; ++i) {
-      HIPCHK(h, hipMalloc(&d.T[i], bytes));
-      HIPCHK(h, hipMalloc(&d.chi[i], bytes));
+    // all ten or none: a later call takes e0 for all of them
+    double **bufs[] = {&d.e0,   &d.y[0],   &d.y[1],   &d.y[2], &d.T[0],
+                       &d.T[1], &d.chi[0], &d.chi[1], &d.M0,   &d.cv0};
+    hipError_t e = hipSuccess;
+    for (double **b : bufs)
+      if (e == hipSuccess) e = hipMalloc(b, sizeof(double) * c.ncell);
+    if (e != hipSuccess) {
+      for (double **b : bufs) {
+        (void)hipFree(*b);
+        *b = nullptr;
+      }
+      return hip_fail(h, e, "hipMalloc diffusion buffers");
     }
-    HIPCHK(h, hipMalloc(&d.M0, bytes));
-    HIPCHK(h, hipMalloc(&d.cv0, bytes));
   }
   const bool limit = nsts <= 0;
   if (limit) {

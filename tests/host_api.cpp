@@ -14,6 +14,7 @@ bool fails(long &k) { return k > 0 && --k == 0; }
 // are an address only
 std::map<void *, size_t> held;
 long live = 0;
+long missing = 0;  // null buffers of diffusion launches
 }  // namespace
 
 void *operator new(size_t n) {
@@ -94,9 +95,14 @@ hipError_t launch_diff_init(const Ctx &, const double *, const double *, const d
                             const double *, const double *) {
   return hipSuccess;
 }
-hipError_t launch_diff_stage(const Ctx &, const double *, const double *, const double *,
-                             const double *, const double *, const double *, double *, double *,
-                             double *, int, int, double, double, double, double, double) {
+hipError_t launch_diff_stage(const Ctx &c, const double *, const double *Ta, const double *chia,
+                             const double *y0, const double *y1, const double *y2, double *yn,
+                             double *Tb, double *chib, int, int, double, double, double, double,
+                             double) {
+  for (const void *p : {(const void *)Ta, (const void *)chia, (const void *)y0, (const void *)y1,
+                        (const void *)y2, (const void *)yn, (const void *)Tb, (const void *)chib,
+                        (const void *)c.diff.M0, (const void *)c.diff.cv0})
+    missing += !p;
   return hipSuccess;
 }
 hipError_t launch_diff_finish(const Ctx &, double *, const double *, const double *, int,
@@ -269,12 +275,39 @@ int host_memory(char **) {
   return 0;
 }
 
+// A super step whose k-th device allocation fails, then one that succeeds: super
+// steps failed, launches with a buffer missing, device buffers left.
+int diffusion(char **) {
+  long failed = 0, live_after = 0;
+  for (long k = 1;; ++k) {
+    const mhd_grid_desc d = desc(8, 6, 4, MHD_PREC_FP64, MHD_EOS_GASRAD);
+    mhd_ctx *h = nullptr;
+    std::vector<double> u(5 * 8 * 6 * 4, 1.0);
+    if (mhd_init_grid(&d, nullptr, &h) ||
+        mhd_set_state(h, u.data(), u.data(), u.data(), u.data(), nullptr, MHD_HOST) ||
+        mhd_set_opacity(h, 1.0, 0.0, 0.0, 1.0))
+      return 1;
+    fail_malloc = k;
+    const int rc = mhd_diffuse(h, 1.0, 4, MHD_DIFF_EINT, nullptr);
+    const bool hit = fail_malloc == 0;
+    fail_malloc = 0;
+    failed += hit && rc != MHD_OK;
+    if (mhd_diffuse(h, 1.0, 4, MHD_DIFF_EINT, nullptr)) return 1;
+    mhd_destroy(h);
+    live_after = live;
+    if (!hit) break;
+  }
+  std::printf("%ld %ld %ld\n", failed, missing, live_after);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::map<std::string, std::pair<int, int (*)(char **)>> commands = {
       {"split", {4, split}}, {"segment", {4, segment}}, {"dsegment", {3, dsegment}},
-      {"sources", {1, sources}}, {"host_memory", {0, host_memory}}};
+      {"sources", {1, sources}}, {"host_memory", {0, host_memory}},
+      {"diffusion", {0, diffusion}}};
   const auto it = argc > 1 ? commands.find(argv[1]) : commands.end();
   if (it == commands.end() || argc - 2 != it->second.first) return 2;
   return it->second.second(argv + 2);

@@ -89,3 +89,9 @@ def test_failed_host_allocation_is_an_error_code(api):
     calls, reached, thrown, missed, live = map(int, api("host_memory"))
     assert reached >= 2 * calls
     assert (thrown, missed, live) == (0, 0, 0)
+
+
+# the ten buffers of the diffusion are there together or not at all
+def test_failed_allocation_of_a_diffusion_buffer(api):
+    failed, missing, live = map(int, api("diffusion"))
+    assert (failed, missing, live) == (10, 0, 0)

@@ -26,6 +26,7 @@ int fail(mhd_ctx *h, int code, const std::string &msg) {
 }
 
 int hip_fail(mhd_ctx *h, hipError_t e, const char *what) {
+  (void)hipGetLastError();  // the runtime keeps it for the next launch to report
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
   return fail(h, MHD_ERR_HIP, m);
 }
@@ -336,6 +337,7 @@ int mhd_init_grid(const mhd_grid_desc *desc, void *hip_stream, mhd_ctx **out) {
   auto cleanup = [&](hipError_t e, const char *what) {
     g_init_err = std::string(what) + ": " + hipGetErrorString(e);
     mhd_destroy(h);
+    (void)hipGetLastError();
     return MHD_ERR_HIP;
   };
   hipError_t e;

@@ -14,6 +14,7 @@ bool fails(long &k) { return k > 0 && --k == 0; }
 // are an address only
 std::map<void *, size_t> held;
 long live = 0;
+hipError_t last_error = hipSuccess;  // as the runtime keeps it until it is read
 long missing = 0;  // null buffers of diffusion launches
 }  // namespace
 
@@ -27,6 +28,11 @@ void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "failure"; }
+hipError_t hipGetLastError() {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
 hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
@@ -37,7 +43,7 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v 
 hipError_t hipMalloc(void **p, size_t bytes) {
   static size_t next = 4096;
   *p = nullptr;
-  if (fails(fail_malloc)) return hipErrorOutOfMemory;
+  if (fails(fail_malloc)) return last_error = hipErrorOutOfMemory;
   *p = bytes <= 1 << 20 ? std::calloc(bytes, 1) : reinterpret_cast<void *>(next += 4096);
   const long k = fail_new;  // not of the map's own
   fail_new = 0;
@@ -103,7 +109,7 @@ hipError_t launch_diff_stage(const Ctx &c, const double *, const double *Ta, con
                         (const void *)y2, (const void *)yn, (const void *)Tb, (const void *)chib,
                         (const void *)c.diff.M0, (const void *)c.diff.cv0})
     missing += !p;
-  return hipSuccess;
+  return hipGetLastError();  // as every launch does
 }
 hipError_t launch_diff_finish(const Ctx &, double *, const double *, const double *, int,
                               double *) {
@@ -275,13 +281,17 @@ int host_memory(char **) {
   return 0;
 }
 
-// A super step whose k-th device allocation fails, then one that succeeds: super
-// steps failed, launches with a buffer missing, device buffers left.
+// A grid that could not be created, then a super step whose k-th device allocation fails, then one that succeeds: super
+// steps failed, launches with a buffer missing, second ones failed
+// (or the next launch after the grid), device buffers left.
 int diffusion(char **) {
-  long failed = 0, live_after = 0;
+  long failed = 0, refused = 0, live_after = 0;
+  const mhd_grid_desc d = desc(8, 6, 4, MHD_PREC_FP64, MHD_EOS_GASRAD);
+  mhd_ctx *h = nullptr;
+  fail_malloc = 5;
+  if (mhd_init_grid(&d, nullptr, &h) != MHD_ERR_HIP) return 1;
+  refused += hipGetLastError() != hipSuccess;
   for (long k = 1;; ++k) {
-    const mhd_grid_desc d = desc(8, 6, 4, MHD_PREC_FP64, MHD_EOS_GASRAD);
-    mhd_ctx *h = nullptr;
     std::vector<double> u(5 * 8 * 6 * 4, 1.0);
     if (mhd_init_grid(&d, nullptr, &h) ||
         mhd_set_state(h, u.data(), u.data(), u.data(), u.data(), nullptr, MHD_HOST) ||
@@ -292,12 +302,12 @@ int diffusion(char **) {
     const bool hit = fail_malloc == 0;
     fail_malloc = 0;
     failed += hit && rc != MHD_OK;
-    if (mhd_diffuse(h, 1.0, 4, MHD_DIFF_EINT, nullptr)) return 1;
+    refused += mhd_diffuse(h, 1.0, 4, MHD_DIFF_EINT, nullptr) != MHD_OK;
     mhd_destroy(h);
     live_after = live;
     if (!hit) break;
   }
-  std::printf("%ld %ld %ld\n", failed, missing, live_after);
+  std::printf("%ld %ld %ld %ld\n", failed, missing, refused, live_after);
   return 0;
 }
 

@@ -91,7 +91,8 @@ def test_failed_host_allocation_is_an_error_code(api):
     assert (thrown, missed, live) == (0, 0, 0)
 
 
-# the ten buffers of the diffusion are there together or not at all
+# the ten buffers of the diffusion are there together or not at all, and the
+# call after a failed one does not report its error again
 def test_failed_allocation_of_a_diffusion_buffer(api):
-    failed, missing, live = map(int, api("diffusion"))
-    assert (failed, missing, live) == (10, 0, 0)
+    failed, missing, refused, live = map(int, api("diffusion"))
+    assert (failed, missing, refused, live) == (10, 0, 0, 0)

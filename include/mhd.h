@@ -311,7 +311,8 @@ const char *mhd_last_error(const mhd_ctx *ctx);
 int mhd_destroy(mhd_ctx *ctx);
 
 /* Kernel launch geometry of the stage kernel (for tests and profiling):
-   tile edge in cells and z-segment length in planes. */
+   tile edge in cells, planes of the longest segment, blocks of the launch
+   (a block may take several segments). */
 int mhd_launch_info(const mhd_ctx *ctx, int32_t *tile, int32_t *zseg,
                     int32_t *blocks);
 

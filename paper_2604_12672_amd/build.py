@@ -24,10 +24,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # of the accumulation registers first (the kernels without matrix
 # instructions are unaffected).
 # -amdgpu-sched-strategy=max-ilp: with the default strategy the FP64 stage
-# kernel (three waves per SIMD, 168 registers) spills 23 registers and waits
-# for every load in flight at each reload; with this one it fits 165 (256^3
-# stratified box, three steps: 14.8 -> 13.1 ms).  The species and diffusion
-# kernels lose 18 and 3 % with it, so the other files take the default.
+# kernel of the ideal gas without optional features (three waves per SIMD, 168
+# registers) spills 22 registers and waits for every load in flight at each
+# reload; with this one it fits 164 (256^3 stratified box, three steps: 14.8 ->
+# 13.1 ms).  The other kernels of that file run as fast with either; the species
+# and diffusion kernels lose 18 and 3 % with it, so the other files take the
+# default.
 STAGE_SCHED = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 STAGE_FILE = "mhd_kernels.hip"
 FLAGS = [

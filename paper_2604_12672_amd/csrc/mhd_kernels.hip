@@ -225,33 +225,16 @@ __device__ __forceinline__ const StageArgs &stage_args_view() {
   return *(const StageArgs *)a;
 }
 
-#ifndef BZCOL
-#define BZCOL (sizeof(R) == 4)
-#endif
-#ifndef BZCOL
-#define BZCOL false
-#endif
-#ifndef LATEDEF
-#define LATEDEF (!GR)
-#endif
-#ifndef BZCOL
-#define BZCOL false
-#endif
-#ifndef LATEDEF
-#define LATEDEF false
-#endif
-#ifndef RINGFIRST
-#define RINGFIRST GR
-#endif
-#ifndef BZCOL
-#define BZCOL false
-#endif
 // Threads of a stage block: the columns' four waves and, in FP64, four each
 // for the x-faces and the y-faces, in FP32 four for both.  The split is by
 // registers: one wave that does all of a column needs 382 of them in FP64
-// (one wave per SIMD, every latency exposed), a third of it 165 (three waves
-// per SIMD, no value spilled); in FP32 a half fits 128 (two blocks of two
-// waves per SIMD), a third would have to fit 80 for two blocks and spills.
+// (one wave per SIMD, every latency exposed), a third of it fits the 168 of
+// three waves per SIMD; in FP32 a half fits 128 (two blocks of two waves per
+// SIMD), a third would have to fit 80 for two blocks and spills.  Only the
+// ideal-gas variants without optional features fit as they are (164 registers
+// in FP64, 123 in FP32; on one plane 164 and 110).  Vector registers spilled by
+// the others, and on one plane: FP64 ideal gas with features 16 (27), gas +
+// radiation 7 (50), with features 34 (50); FP32 3 (9), 3 (0) and 13 (26).
 // 256^3 stratified box per launch, one wave per column -> split: FP64 3.07 ->
 // 1.95 ms (the launch's 770 M vector instructions take 1.3 ms to issue),
 // 250 x 250 x 310 in FP32 1.81 -> 1.59 ms.
@@ -489,8 +472,9 @@ __device__ __forceinline__ void column_steps(const StageArgs &args, StageLds<R, 
   constexpr int NF = Cfg<R, GR>::NF;
   // FP32 with the optional features: the update is finished at the top of the
   // next step, so its values arrive over the barrier and are not live beside
-  // the forcing (26 spilled registers instead of 37; turbulence box at 384^3
-  // 36.9 -> 34.1 ms for two steps); the others lose 0 to 4 % that way
+  // the forcing (spilled registers 21 -> 3 with the ideal gas, 34 -> 13 with gas
+  // + radiation; turbulence box at 384^3 38.4 -> 31.2 ms for two steps, others
+  // 1 % faster); the other variants lose 0 to 4 % that way
   constexpr bool LATE = sizeof(R) == 4 && XF;
   const int z0 = t.z0, z1 = t.z1;
   R st[ST_N];
@@ -1165,8 +1149,9 @@ constexpr int RED_BLOCKS = CFL_MAX_BLOCKS;
 
 template <bool GR, bool ML>
 // Three waves per SIMD at least: the variant with the learned guess would
-// otherwise take 181 registers (two waves) and wait on memory; at 168 it
-// spills five registers and runs 8 % faster (the other variants use 66).
+// otherwise take 176 registers (two waves) and wait on memory; at 168 it
+// spills one register and runs 11 % faster (184 -> 163 us a launch over 128^3
+// and 256^3 in turn); the other variants use 50 and 70.
 __global__ __launch_bounds__(RED_THREADS) __attribute__((amdgpu_waves_per_eu(3))) void
 signal_speed_kernel(
     Phys ph, const double *__restrict__ U, const double *__restrict__ Bx,
@@ -1373,7 +1358,7 @@ __global__ __launch_bounds__(256) void mlp_guess_kernel(Phys ph, const double *_
   // every lane of a wave runs the matrix passes; lanes past the end repeat
   // the last cell and store nothing
   // cell data of one cell: U and the six faces (read at the top of each
-  // pass: without a prefetch of the next cell the kernel fits 156 registers
+  // pass: without a prefetch of the next cell the kernel fits 160 registers
   // and three waves per SIMD, which hide the latency better)
   auto fetch = [&](size_t q, double u[5], double f[6]) {
     int i, j, k;
@@ -1553,9 +1538,9 @@ hipError_t launch_eos_solve(const Ctx &c, const double *rho, const double *e,
                             const double *tguess, long long n, double *T, double *T0,
                             bool stats) {
   // With the network three rounds of the three resident blocks per CU: each
-  // block stages the 17.5 KB of weights, and with 8192 blocks of a few hundred
-  // samples that was 4 % of the time (4.0 M samples 84.1 -> 78.9 us a call,
-  // 16.8 M 263 -> 260, 0.3 M the same; two rounds 79.4, four 79.6, one 81.5)
+  // block stages the 17.5 KB of weights, 8192 blocks for a few hundred samples
+  // each (4.0 M samples 67.7 -> 63.3 us a call, 16.8 M 256 -> 254, 0.3 M the
+  // same; two rounds 65.0, four 64.8, one 66.8)
   const long long cap = c.d.eos_guess == MHD_GUESS_MLP ? 9ll * c.cus : 8192;
   long long nb = (n + 255) / 256;
   nb = nb < cap ? nb : cap;

@@ -59,7 +59,7 @@ FETCH_FACTOR = 2.0
 WRITE_FACTOR = 1.0
 TRAFFIC_KIB = {
     # digest: {path: (fetch KiB, write KiB) per stage dispatch}
-    "a51c69528243a73c": {"fp64": (1405897.7, 1085419.4), "split": (2425400.5, 1240977.8)},
+    "177141ee3a23295f": {"fp64": (1370208.3, 1080281.2), "split": (2407018.9, 1242006.3)},
 }
 
 
@@ -69,7 +69,7 @@ TRAFFIC_KIB = {
 # wave64 instruction per four cycles, 2.4 GHz) they give the launch's
 # instruction-issue floor: the bound the stage kernel actually meets.
 VALU_INSTS = {
-    "a51c69528243a73c": {"fp64": 770110151, "split": 621045514},
+    "177141ee3a23295f": {"fp64": 770110151, "split": 621045514},
 }
 VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4.0
 
@@ -77,7 +77,7 @@ VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4.0
 # HBM traffic of diff_stage_kernel (FETCH_SIZE, WRITE_SIZE in KiB per
 # dispatch, averaged over a super step) for the digest of its sources
 RKL2_TRAFFIC_KIB = {
-    "697a8c678db4ef6e": {"eint": (521642.4, 397803.5), "temp": (504383.5, 266731.5)},
+    "9829f5cbd30ed7be": {"eint": (525873.5, 397803.5), "temp": (525784.6, 266731.5)},
 }
 
 
